@@ -140,35 +140,50 @@ __device__ __forceinline__ float block_max(float v, float* red) {
   return s;
 }
 
-__device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
-  uint32_t lo = static_cast<uint32_t>(v), hi = static_cast<uint32_t>(v >> 32);
-  lo = __shfl_up(lo, d);
-  hi = __shfl_up(hi, d);
+// Integer scans and sums of one uint64 per lane. The lanes exchange values
+// with DPP moves (a few cycles each) rather than through the LDS crossbar: six
+// shuffle rounds of two dependent ds_bpermute each are ~1400 cycles, which in
+// the one- and two-work-group sampling kernels nothing hides.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {   // lanes without a source get 0
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), CTRL, ROWS, 0xf, false);
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
+__device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
+  v += dpp_u64<0x111, 0xf>(v);   // row_shr:1 .. 8: inclusive within each row of 16 lanes
+  v += dpp_u64<0x112, 0xf>(v);
+  v += dpp_u64<0x114, 0xf>(v);
+  v += dpp_u64<0x118, 0xf>(v);
+  v += dpp_u64<0x142, 0xa>(v);   // row_bcast:15: rows 1 and 3 add the row before them
+  v += dpp_u64<0x143, 0xc>(v);   // row_bcast:31: rows 2 and 3 add the lower half
+  return v;
+}
+// v of lane `src`, which every active lane agrees on.
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int src) {
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(v), src);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), src);
+  return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) { return readlane_u64(wave_incl_scan_u64(v), 63); }
 
 // Exclusive prefix sum of one uint64 per thread over the block (blockDim.x a
-// multiple of 64, <= 1024). `wsum` is __shared__ uint64_t[17]. Returns the
+// multiple of 64, <= 1024). `wsum` is __shared__ uint64_t[16]. Returns the
 // exclusive prefix; *total receives the block total.
 __device__ __forceinline__ uint64_t block_exscan_u64(uint64_t v, uint64_t* wsum, uint64_t* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  uint64_t inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    uint64_t o = shfl_up_u64(inc, d);
-    if (lane >= d) inc += o;
-  }
+  const uint64_t inc = wave_incl_scan_u64(v);
   __syncthreads();
   if (lane == 63) wsum[w] = inc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t acc = 0;
-    for (int i = 0; i < nw; ++i) { uint64_t t = wsum[i]; wsum[i] = acc; acc += t; }
-    wsum[16] = acc;
+  uint64_t before = 0, all = 0;
+  for (int i = 0; i < nw; ++i) {
+    const uint64_t t = wsum[i];
+    before += i < w ? t : 0;
+    all += t;
   }
-  __syncthreads();
-  *total = wsum[16];
-  return wsum[w] + inc - v;
+  *total = all;
+  return before + inc - v;
 }
 
 }  // namespace sps

@@ -27,26 +27,6 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int o) {
   const uint32_t hi = __shfl_xor(static_cast<uint32_t>(v >> 32), o);
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
-__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
-  const uint32_t lo = __shfl(static_cast<uint32_t>(v), src);
-  const uint32_t hi = __shfl(static_cast<uint32_t>(v >> 32), src);
-  return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += shfl_xor_u64(v, o);
-  return v;
-}
-__device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t o = shfl_up_u64(v, d);
-    if (lane >= d) v += o;
-  }
-  return v;
-}
-
 // floor(x 2^32) for x in (0, 1), 2^32 for x >= 1, 0 for x <= 0 or NaN, in
 // fp32 alone: scaling by 2^32 is exact and the conversion truncates; the
 // largest x below 1 gives 2^32 - 256, so x >= 1 takes that and the missing
@@ -405,7 +385,7 @@ __device__ __forceinline__ bool bucket_select(const RowKeys& rk, uint64_t lo, ui
     }
     const uint64_t ic = wave_incl_scan_u64(tc), iw = wave_incl_scan_u64(tw);
     if (NUCLEUS) {
-      const uint64_t W = shfl_u64(iw, 63);
+      const uint64_t W = readlane_u64(iw, 63);
       const uint64_t target = grid_threshold(top_p, W);
       weighted = target != 0;
       need = weighted ? target : 1;
@@ -807,7 +787,7 @@ __device__ bool hist_select(PF pf, const RowIds& ids, int V, uint64_t lo, int lo
     const uint64_t ic = wave_incl_scan_u64(tc), iw = wave_incl_scan_u64(tw);
     bool weighted = false;
     if (NUCLEUS) {
-      const uint64_t W = shfl_u64(iw, 63);
+      const uint64_t W = readlane_u64(iw, 63);
       const uint64_t target = grid_threshold(top_p, W);
       weighted = target != 0;
       need = weighted ? target : 1;
@@ -1101,7 +1081,7 @@ __global__ __launch_bounds__(kCutSegThreads) void draft_draw_kernel(const char* 
                                                                     int32_t* __restrict__ tokens,
                                                                     const int32_t* __restrict__ ctx, uint64_t seed,
                                                                     uint64_t loop, int* err) {
-  __shared__ uint64_t wsum[17];
+  __shared__ uint64_t wsum[16];
   __shared__ uint64_t s_thr, s_off;
   __shared__ int s_seg, s_y;
   const int b = blockIdx.x, tid = threadIdx.x;
@@ -1113,17 +1093,12 @@ __global__ __launch_bounds__(kCutSegThreads) void draft_draw_kernel(const char* 
   if (tid < 64) {
     const float u = philox_uniform(seed, loop, 0, b, t);
     const uint64_t tot = tid < nseg ? cs.n[tid] : 0;
-    uint64_t inc = tot;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint64_t o = shfl_up_u64(inc, d);
-      if (tid >= d) inc += o;
-    }
-    const uint64_t W = shfl_u64(inc, 63);
+    const uint64_t inc = wave_incl_scan_u64(tot);
+    const uint64_t W = readlane_u64(inc, 63);
     const uint64_t thr = grid_threshold(u, W);
     const uint64_t hit = W ? __ballot(tid < nseg && inc > thr) : 0;
     const int sstar = hit ? __ffsll(static_cast<long long>(hit)) - 1 : -1;
-    const uint64_t off = shfl_u64(inc - tot, sstar < 0 ? 0 : sstar);   // weight before segment sstar
+    const uint64_t off = readlane_u64(inc - tot, sstar < 0 ? 0 : sstar);   // weight before segment sstar
     if (tid == 0) {
       s_thr = thr;
       s_off = off;
@@ -1207,7 +1182,7 @@ __device__ __forceinline__ uint64_t segment_total(WF wf, Segment sg) {
 
 // Block-wide integer inverse-CDF draw with weights wf(i), i < V, given every
 // wave's segment total `tot` (from segment_total). s_tot is __shared__
-// uint64_t[16 + 1], s_res a __shared__ int. Returns the drawn index to every
+// uint64_t[16], s_res a __shared__ int. Returns the drawn index to every
 // thread, or -1 when all weights are zero (W == 0). The wave whose segment
 // holds the threshold reads it again (now cache-resident) with lane l owning
 // kScanPerLane consecutive entries of a super-chunk, scans the lane totals and
@@ -1240,8 +1215,7 @@ __device__ int block_draw(WF wf, Segment sg, uint64_t tot, float u, uint64_t* s_
         lt += w[k];
       }
       const uint64_t inc = wave_incl_scan_u64(lt);
-      const uint64_t all = (static_cast<uint64_t>(__shfl(static_cast<uint32_t>(inc >> 32), 63)) << 32) |
-                           __shfl(static_cast<uint32_t>(inc), 63);
+      const uint64_t all = readlane_u64(inc, 63);
       if (run + all > thr) {               // wave-uniform
         const uint64_t ex = run + inc - lt;
         if (ex <= thr && thr < ex + lt) {  // exactly one lane
@@ -1324,37 +1298,44 @@ __device__ __forceinline__ int accept_draw(const Row& qr, const float* __restric
 }
 
 // The accept tests of sequence b, left to right, r_t p_t(x~_t) < q_t(x~_t)
-// exact in fp64 (wave 0 of the work-group; lane t tests draft t): a = the
+// exact in fp64 (one wave of the work-group; lane t tests draft t): a = the
 // first rejected draft (K if none), bad = x~_a is out of range, nf = a value
-// the tests read or a target row of the sequence is non-finite. Every lane
-// of the wave returns the same values. drafts[t] is x~_{t+1}.
+// the tests read or a target row of the sequence is non-finite, u = the
+// uniform of the final draw. Every lane of the wave returns the same values.
+// drafts[t] is x~_{t+1}. Lane t < K forms r_t and lane K u in one Philox
+// evaluation (~400 VALU instructions), which runs while the drafts load.
 template <class QS>
 __device__ __forceinline__ void accept_tests(const QS& qs, const float* __restrict__ p,
                                              const int32_t* __restrict__ dr, const float* __restrict__ unif,
                                              uint64_t seed, uint64_t loop, int K, int V, int b, int* a_out,
-                                             bool* bad_out, bool* nf_out) {
-  const int tid = threadIdx.x;
+                                             bool* bad_out, bool* nf_out, float* u_out) {
+  const int lane = threadIdx.x & 63;
+  const int x = lane < K ? dr[lane] : 0;
+  float r = 0.f;
+  if (lane <= K)
+    r = unif ? unif[b * (K + 1) + lane] : philox_uniform(seed, loop, lane < K ? 1 : 2, b, lane < K ? lane : 0);
   bool rejected = false, bad = false, nf = false;
-  if (tid < K) {
-    const int x = dr[tid];
-    if (x < 0 || x >= V) {
-      bad = true;
-      rejected = true;
-    } else {
-      const float rho = qs.row(b * (K + 1) + tid)(x);
-      const float pi = p[(static_cast<size_t>(b) * K + tid) * V + x];
-      const float r = unif ? unif[b * (K + 1) + tid] : philox_uniform(seed, loop, 1, b, tid);
-      nf = not_finite(rho) | not_finite(pi);
-      rejected = !(static_cast<double>(r) * static_cast<double>(pi) < static_cast<double>(rho));
+  if (lane <= K) {
+    const typename QS::Row qr = qs.row(b * (K + 1) + lane);
+    nf = qr.nonfinite();
+    if (lane < K) {
+      bad = x < 0 || x >= V;
+      rejected = bad;
+      if (!bad) {
+        const float rho = qr(x);
+        const float pi = p[(static_cast<size_t>(b) * K + lane) * V + x];
+        nf |= not_finite(rho) | not_finite(pi);
+        rejected = !(static_cast<double>(r) * static_cast<double>(pi) < static_cast<double>(rho));
+      }
     }
   }
-  if (tid <= K) nf |= qs.row(b * (K + 1) + tid).nonfinite();
   const uint64_t rej = __ballot(rejected);
   const uint64_t badm = __ballot(bad);
   *nf_out = __ballot(nf) != 0;                     // wave-wide, outside any branch
   const int a = rej ? __ffsll(static_cast<long long>(rej)) - 1 : K;
   *a_out = a;
   *bad_out = a < K && ((badm >> a) & 1ull) != 0;
+  *u_out = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(r), K));
 }
 
 // The outcome of sequence b from a and the draw y (-2: a non-finite value
@@ -1388,7 +1369,8 @@ __global__ __launch_bounds__(kSampleThreads) void accept_kernel(QS qs, const flo
                                                                 int32_t* __restrict__ out,
                                                                 int32_t* __restrict__ n_acc, int* err) {
   __shared__ int s_a, s_y, s_nf;
-  __shared__ uint64_t wsum[17];
+  __shared__ float s_u;
+  __shared__ uint64_t wsum[16];
   const int b = blockIdx.x, tid = threadIdx.x;
   const int32_t* dr = drafts + static_cast<size_t>(b) * dstride + doff;
 
@@ -1396,12 +1378,14 @@ __global__ __launch_bounds__(kSampleThreads) void accept_kernel(QS qs, const flo
   if (tid < 64) {
     int a;
     bool bad, nf;
-    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf);
+    float u;
+    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
     if (tid == 0) {
       if (bad) atomicOr(err, kErrBadToken);
       s_a = a;
       s_y = 0;
       s_nf = nf;
+      s_u = u;
     }
   }
   __syncthreads();
@@ -1415,9 +1399,136 @@ __global__ __launch_bounds__(kSampleThreads) void accept_kernel(QS qs, const flo
   int y = -2;
   if (!nf_in) {                            // uniform over the block
     const typename QS::Row qr = qs.row(row);
-    const float u = unif ? unif[b * (K + 1) + K] : philox_uniform(seed, loop, 2, b, 0);
+    const float u = s_u;
     y = qr.modified() ? accept_draw<true>(qr, prow, resid, V, u, wsum, &s_y)
                       : accept_draw<false>(qr, prow, resid, V, u, wsum, &s_y);
+  }
+  accept_finish(b, a, y, dr, K, out, n_acc, err);
+}
+
+// The entry row that holds the threshold: lane l has the weights of entries
+// 64 k + l in v[k], off is the weight before them. Halves the range of k on
+// wave sums; leaves the chosen row's weights in v[0], its k added to k0 and
+// the weight before it in off.
+template <int WIDTH, int N>
+__device__ __forceinline__ void halve_to_entry(uint32_t (&v)[N], uint64_t thr, uint64_t& off, int& k0) {
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int k = 0; k < WIDTH; ++k) hi += __builtin_uadd_overflow(lo, v[k], &lo);
+  const uint64_t half = wave_sum_u64(static_cast<uint64_t>(hi) << 32 | lo);
+  const bool up = off + half <= thr;
+  off += up ? half : 0;
+  k0 += up ? WIDTH : 0;
+#pragma unroll
+  for (int k = 0; k < WIDTH; ++k) v[k] = up ? v[k + WIDTH] : v[k];
+  if constexpr (WIDTH > 1) halve_to_entry<WIDTH / 2>(v, thr, off, k0);
+}
+
+// fixed_weight of x < 1, in 32 bits (0 for NaN).
+__device__ __forceinline__ uint32_t fixed_weight32(float x) {
+  return static_cast<uint32_t>(fminf(fmaxf(x, 0.f), 0x1.fffffep-1f) * 4294967296.0f);
+}
+
+// The accept / resample of one sequence on given distributions, V <= PER
+// kSampleThreads: the outcome of accept_kernel<QProbs> with the final draw's
+// row pair read once. Wave w owns the vocabulary segment wave_segment gives
+// it, and lane l keeps the draw weights of its entries 64 k + l, k < PER, in
+// registers. The segment totals name the wave whose segment holds the
+// threshold, and that wave alone halves its k range on wave sums and scans
+// one entry per lane. Rows with an entry of 1 or more (weight 2^32: one-hot
+// rows) and zero residuals take the two-pass draw. One work-group per
+// sequence (the call has no scratch to meet in), so what bounds it is the
+// chain of memory rounds (drafts, gathers, rows) and the VALU work of a row
+// on one CU. Against the two-pass draw over 64-bit weights (kernel time): 64
+// rows of 32000 (K = 8) 22.1 -> 9.6 us, one row (K = 4) 20.6 -> 8.3.
+template <int PER>
+__global__ __launch_bounds__(kSampleThreads) void accept_probs_kernel(
+    const float* __restrict__ q, const float* __restrict__ p, const int32_t* __restrict__ drafts,
+    const float* __restrict__ unif, uint64_t seed, uint64_t loop, int K, int V, int32_t* __restrict__ out,
+    int32_t* __restrict__ n_acc, int* err) {
+  __shared__ int s_a, s_y, s_nf;
+  __shared__ float s_u;
+  __shared__ uint64_t s_tot[kSampleThreads / 64];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int32_t* dr = drafts + static_cast<size_t>(b) * K;
+  const QProbs qs{q, V};
+  if (tid < 64) {
+    int a;
+    bool bad, nf;
+    float u;
+    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
+    if (tid == 0) {
+      if (bad) atomicOr(err, kErrBadToken);
+      s_a = a;
+      s_y = -1;
+      s_nf = nf;
+      s_u = u;
+    }
+  }
+  __syncthreads();
+  // Wave-uniform values in scalar registers, as the row descriptors need them:
+  // a row ends at the wave's segment for it, and entries past that read 0.
+  const int a = __builtin_amdgcn_readfirstlane(s_a);
+  const int S = ((V + kSampleThreads / 64 - 1) / (kSampleThreads / 64) + 63) & ~63;
+  const int b0 = min(V, __builtin_amdgcn_readfirstlane(wave) * S), b1 = min(V, b0 + S);
+  const auto row = [&](const float* base, size_t r) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + r * V), 0, b1 * 4, 0x00027000);
+  };
+  const bool resid = a < K;                // draw from (q - p)_+, else from q
+  int y = -2;
+  if (!s_nf) {                             // uniform over the block
+    const __amdgpu_buffer_rsrc_t qrow = row(q, static_cast<size_t>(b) * (K + 1) + a);
+    const __amdgpu_buffer_rsrc_t prow = row(p, resid ? static_cast<size_t>(b) * K + a : 0);
+    // Batches of kB entries, the next batch's loads in flight while one is
+    // summed (all 2 PER loads at once do not fit beside the weights).
+    constexpr int kB = 8;
+    uint32_t xq[2][kB], xp[2][kB];
+    auto load = [&](int k0, uint32_t (&vq)[kB], uint32_t (&vp)[kB]) {
+      const int at = (b0 + 64 * k0 + lane) * 4;
+#pragma unroll
+      for (int k = 0; k < kB; ++k) vq[k] = __builtin_amdgcn_raw_buffer_load_b32(qrow, at + 256 * k, 0, 0);
+#pragma unroll
+      for (int k = 0; k < kB; ++k) vp[k] = resid ? __builtin_amdgcn_raw_buffer_load_b32(prow, at + 256 * k, 0, 0) : 0;
+    };
+    uint32_t w[PER], tot_lo = 0, tot_hi = 0;
+    uint32_t worst = 0;                    // the largest |x| as bits: Inf and NaN above every number
+    load(0, xq[0], xp[0]);
+#pragma unroll
+    for (int k0 = 0; k0 < PER; k0 += kB) {
+      if (k0 + kB < PER) load(k0 + kB, xq[(k0 / kB + 1) & 1], xp[(k0 / kB + 1) & 1]);
+#pragma unroll
+      for (int j = 0; j < kB; ++j) {
+        const uint32_t vq = xq[(k0 / kB) & 1][j], vp = xp[(k0 / kB) & 1][j];
+        worst = max(worst, max(vq << 1, vp << 1));
+        const uint32_t wq = fixed_weight32(__uint_as_float(vq)), wp = fixed_weight32(__uint_as_float(vp));
+        w[k0 + j] = __builtin_elementwise_sub_sat(wq, wp);
+        tot_hi += __builtin_uadd_overflow(tot_lo, w[k0 + j], &tot_lo);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const uint64_t tot = wave_sum_u64(static_cast<uint64_t>(tot_hi) << 32 | tot_lo);
+    if (lane == 0) s_tot[wave] = tot;
+    const bool one = __syncthreads_or(worst >= 0x3f800000u << 1);   // an entry of magnitude >= 1, or not finite
+    uint64_t off = 0, W = 0;
+    for (int v = 0; v < kSampleThreads / 64; ++v) {
+      const uint64_t t = s_tot[v];
+      off += v < wave ? t : 0;
+      W += t;
+    }
+    if (one || W == 0) {                   // uniform, as W and thr
+      y = accept_draw<false>(qs.row(b * (K + 1) + a), p + (resid ? static_cast<size_t>(b) * K + a : 0) * V, resid, V,
+                             s_u, s_tot, &s_y);
+    } else {
+      const uint64_t thr = grid_threshold(s_u, W);
+      if (off <= thr && thr < off + tot) {   // wave-uniform: the crossing lies in this wave's segment
+        int k0 = 0;
+        halve_to_entry<PER / 2>(w, thr, off, k0);
+        const uint64_t hit = __ballot(off + wave_incl_scan_u64(w[0]) > thr);
+        if (lane == 0) s_y = b0 + 64 * k0 + __ffsll(static_cast<long long>(hit)) - 1;
+      }
+      __syncthreads();
+      y = s_y;
+    }
   }
   accept_finish(b, a, y, dr, K, out, n_acc, err);
 }
@@ -1473,7 +1584,8 @@ __global__ __launch_bounds__(kCutSegThreads) void accept_part_kernel(QS qs, cons
   if (tid < 64) {
     int a;
     bool bad, nf;
-    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf);
+    float u;
+    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
     if (tid == 0) {
       s_a = a;
       s_nf = nf;
@@ -1531,7 +1643,7 @@ __global__ __launch_bounds__(kCutSegThreads) void accept_draw_kernel(QS qs, cons
                                                                      int nseg, int seg, int32_t* __restrict__ out,
                                                                      int32_t* __restrict__ n_acc, int* err) {
   static_assert(kMaxRowSegments <= 64, "one wave holds the segment totals");
-  __shared__ uint64_t wsum[17];
+  __shared__ uint64_t wsum[16];
   __shared__ uint64_t s_thr, s_off;
   __shared__ int s_seg, s_y, s_mode;
   const int b = blockIdx.x, tid = threadIdx.x;
@@ -1548,23 +1660,15 @@ __global__ __launch_bounds__(kCutSegThreads) void accept_draw_kernel(QS qs, cons
     const bool in = tid < nseg;
     const bool nf = __ballot(in && cs.n[kAccNf + tid] != 0) != 0;
     const uint64_t tr = in ? cs.n[tid] : 0, tq = in ? cs.w[tid] : 0;
-    uint64_t ir = tr, iq = tq;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint64_t o1 = shfl_up_u64(ir, d), o2 = shfl_up_u64(iq, d);
-      if (tid >= d) {
-        ir += o1;
-        iq += o2;
-      }
-    }
-    const uint64_t Wr = shfl_u64(ir, 63), Wq = shfl_u64(iq, 63);
+    const uint64_t ir = wave_incl_scan_u64(tr), iq = wave_incl_scan_u64(tq);
+    const uint64_t Wr = readlane_u64(ir, 63), Wq = readlane_u64(iq, 63);
     const bool use_r = resid && Wr != 0;
     const uint64_t W = use_r ? Wr : Wq, inc = use_r ? ir : iq, tot = use_r ? tr : tq;
     const float u = unif ? unif[b * (K + 1) + K] : philox_uniform(seed, loop, 2, b, 0);
     const uint64_t thr = grid_threshold(u, W);
     const uint64_t hit = W ? __ballot(in && inc > thr) : 0;
     const int sstar = hit ? __ffsll(static_cast<long long>(hit)) - 1 : -1;
-    const uint64_t off = shfl_u64(inc - tot, sstar < 0 ? 0 : sstar);
+    const uint64_t off = readlane_u64(inc - tot, sstar < 0 ? 0 : sstar);
     if (tid == 0) {
       s_thr = thr;
       s_off = off;
@@ -1625,7 +1729,7 @@ __global__ __launch_bounds__(kSampleThreads) void draft_sample_kernel(
     const int32_t* __restrict__ ctx, uint64_t seed, uint64_t loop, int* err) {
   __shared__ float red[32];
   __shared__ int ired[16];
-  __shared__ uint64_t wsum[17];
+  __shared__ uint64_t wsum[16];
   __shared__ int s_y;
   __shared__ CutScratch sc;
   extern __shared__ uint32_t s_rowkeys[];
@@ -1751,8 +1855,17 @@ hipError_t launch_row_softmax(const float* logits, int rows, int V, float temper
 hipError_t launch_accept_probs(const float* p, const float* q, const int32_t* drafts, const float* unif,
                                uint64_t seed, uint64_t loop, int B, int K, int V, int32_t* out, int32_t* n_acc,
                                int* err, hipStream_t st) {
-  hipLaunchKernelGGL(accept_kernel<QProbs>, dim3(B), dim3(kSampleThreads), 0, st, QProbs{q, V}, p, drafts, K, 0,
-                     unif, seed, loop, K, V, out, n_acc, err);
+  // Rows that fit a work-group's registers (8 or 32 entries per thread) are
+  // read once; longer ones take the two-pass draw.
+  if (V <= 8 * kSampleThreads)
+    hipLaunchKernelGGL(accept_probs_kernel<8>, dim3(B), dim3(kSampleThreads), 0, st, q, p, drafts, unif, seed, loop,
+                       K, V, out, n_acc, err);
+  else if (V <= kPerLane * kSampleThreads)
+    hipLaunchKernelGGL(accept_probs_kernel<kPerLane>, dim3(B), dim3(kSampleThreads), 0, st, q, p, drafts, unif, seed,
+                       loop, K, V, out, n_acc, err);
+  else
+    hipLaunchKernelGGL(accept_kernel<QProbs>, dim3(B), dim3(kSampleThreads), 0, st, QProbs{q, V}, p, drafts, K, 0,
+                       unif, seed, loop, K, V, out, n_acc, err);
   return hipGetLastError();
 }
 

@@ -118,6 +118,44 @@ def test_accept_degenerate_cases(sps):
     assert sps.device_error() == 0
 
 
+@pytest.mark.parametrize("V", [2, 63, 64, 65, 1023, 1025, 8191, 8192, 8193, 32767, 32768, 32769])
+def test_accept_row_lengths(sps, V):
+    """Row lengths at the edges of the accept kernels' segments, register
+    batches and dispatch; each sequence of the batch one kind of row: ordinary
+    (residual and bonus draws over the whole range of u), one-hot, zero
+    residual, and weights of 2^32 beside ordinary ones. Bit-exact."""
+    K = 2
+    g = np.random.default_rng(V)
+    u = [0.0, 0.11, 0.5, 0.77, 0.999, 1 - 2.0 ** -24]
+    kinds = [("plain", r, x) for x in u for r in (0.0, 1 - 2.0 ** -24)] + \
+            [(k, 0.75, x) for k in ("onehot", "zero", "ones") for x in (0.0, 0.6, 0.999)]
+    B = len(kinds)
+    z = g.normal(0, 2, size=(B, K + 1, V))
+    q = np.exp(z)
+    q = (q / q.sum(-1, keepdims=True)).astype(np.float32)
+    p = np.exp(z[:, :K] + g.normal(0, 0.5, size=(B, K, V)))
+    p = (p / p.sum(-1, keepdims=True)).astype(np.float32)
+    unif = np.zeros((B, K + 1), np.float32)
+    for b, (kind, r, x) in enumerate(kinds):
+        unif[b] = [r, r, x]
+        hot = [int(v) for v in g.integers(0, V, 3)]
+        if kind == "onehot":
+            q[b], p[b] = 0, 0
+            q[b, range(3), hot] = 1
+            p[b, range(2), [hot[0], (hot[1] + 1) % V]] = 1
+        elif kind == "zero":                          # q <= p everywhere: nothing left of q - p
+            p[b] = q[b, :K] * np.float32(2)
+        elif kind == "ones":                          # not distributions: several entries of 1 or more
+            q[b, :, [0, V - 1]] = 1
+            q[b, :, V // 2] = np.float32(1.5)
+    drafts = np.argmax(p, axis=-1).astype(np.int32)
+    out, nacc = run_accept(sps, p, q, drafts, unif)
+    w_out, w_n, _ = oacc.accept_resample(p, q, drafts, unif)
+    np.testing.assert_array_equal(out, w_out)
+    np.testing.assert_array_equal(nacc, w_n)
+    assert sps.device_error() == 0
+
+
 def test_accept_k0_is_a_draw_from_q(sps):
     q = np.random.default_rng(5).dirichlet(np.ones(1000), size=(16, 1)).astype(np.float32)
     unif = np.linspace(0, 1, 16, endpoint=False, dtype=np.float32)[:, None]
