@@ -83,22 +83,22 @@ hipError_t launch_kv_copy(int dtype, int to_cache, void* kc, void* vc, int H, in
 // Sampling.
 // Row statistics (stats, row_stat_bytes() each, may be NULL) and, if probs
 // != NULL, the probabilities after temperature and the top-k / nucleus
-// modifiers (top_k <= 0 or >= V: off; top_p >= 1: off). With stats and cut
-// (rows x cut_row_bytes(V) bytes of scratch) given, rows with a modifier are
-// cut over several CUs; otherwise one work-group per row does everything.
+// modifiers (top_k <= 0 or >= V: off; top_p >= 1: off), one work-group per row.
 hipError_t launch_row_softmax(const float* logits, int rows, int V, float temperature, int top_k, float top_p,
-                              void* stats, float* probs, char* cut, int* err, hipStream_t st);
+                              void* stats, float* probs, int* err, hipStream_t st);
 hipError_t launch_accept_probs(const float* p, const float* q, const int32_t* drafts,
                                const float* unif, uint64_t seed, uint64_t loop, int B, int K,
                                int V, int32_t* out, int32_t* n_acc, int* err, hipStream_t st);
-// The verify step's fused accept / resample (q from the logits and their
-// row statistics). cut (B x cut_row_bytes(V) bytes of scratch), if given,
-// takes the final draw over several CUs (V up to the cut-off's largest
-// row); otherwise one work-group per sequence does all.
-hipError_t launch_accept_logits(const float* p, const float* logits, const void* stats,
-                                float temperature, const int32_t* tokens, const float* unif,
-                                uint64_t seed, uint64_t loop, int B, int K, int V, int32_t* out,
-                                int32_t* n_acc, char* cut, int* err, hipStream_t st);
+// The verify step after its logits (B (K + 1) rows): the row statistics into
+// stats, the q rows into probs (may be NULL) and, if accept, the fused accept
+// / resample with q from the logits. cut is scratch of B (K + 1)
+// cut_row_bytes(V) bytes. At temperature > 0 and V up to the cut-off's
+// largest row everything runs over several CUs; otherwise the statistics,
+// and past that V the draw too, take one work-group per row.
+hipError_t launch_verify_tail(const float* logits, int B, int K, int V, float temperature, int top_k, float top_p,
+                              void* stats, char* cut, float* probs, bool accept, const float* p,
+                              const int32_t* tokens, const float* unif, uint64_t seed, uint64_t loop, int32_t* out,
+                              int32_t* n_acc, int* err, hipStream_t st);
 // Draft step t: p_t of each sequence's last row into p_out and x~_{t+1}
 // drawn from it. stats (B rows) and cut (B x cut_row_bytes(V)), if given,
 // are scratch for the statistics, the cut (when a modifier is on), the

@@ -1004,25 +1004,6 @@ __global__ __launch_bounds__(kSampleThreads) void cut_select_kernel(const float*
   if (threadIdx.x == 0) stats[r] = st;
 }
 
-// Probabilities of rows (with their cut) into probs[row][V], one segment per
-// work-group: grid (segments, rows).
-__global__ __launch_bounds__(kCutSegThreads) void cut_export_kernel(const float* __restrict__ logits, int V,
-                                                                    float temperature,
-                                                                    const RowStat* __restrict__ stats,
-                                                                    float* __restrict__ probs, int seg) {
-  const int r = blockIdx.y, s = blockIdx.x;
-  const RowStat st = stats[r];
-  const float* z = logits + static_cast<size_t>(r) * V;
-  float* pr = probs + static_cast<size_t>(r) * V;
-  const float inv_t = 1.0f / temperature;
-  const int i0 = s * seg, i1 = min(V, i0 + seg);
-  if (row_modified(st)) {
-    for (int i = i0 + static_cast<int>(threadIdx.x); i < i1; i += kCutSegThreads) pr[i] = prob_final<true>(z[i], st, inv_t, i);
-  } else {
-    for (int i = i0 + static_cast<int>(threadIdx.x); i < i1; i += kCutSegThreads) pr[i] = prob_final<false>(z[i], st, inv_t, i);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // The draft step's softmax export and draw over several CUs (temperature >
 // 0): draft_p_kernel's work-groups take one segment of a sequence's row
@@ -1033,15 +1014,32 @@ __global__ __launch_bounds__(kCutSegThreads) void cut_export_kernel(const float*
 // that segment. The draw is the one of draft_sample_kernel (integer inverse
 // CDF over the stored probabilities, in index order).
 // ---------------------------------------------------------------------------
+// use(i, ld(i)) for the entries [i0, i1) of a segment, kSegBatch loads of a
+// thread in flight together (a loop of single entries waits for each: the
+// stores may alias the next load: the tail over 5 rows 8.2 -> 7.5 us, over 144
+// 40.3 -> 36.4).
+constexpr int kSegBatch = 4;
+template <class LD, class USE>
+__device__ __forceinline__ void for_segment(int i0, int i1, LD ld, USE use) {
+  for (int base = i0 + static_cast<int>(threadIdx.x); base < i1; base += kSegBatch * kCutSegThreads) {
+    decltype(ld(0)) x[kSegBatch];
+#pragma unroll
+    for (int k = 0; k < kSegBatch; ++k) x[k] = ld(min(base + k * kCutSegThreads, i1 - 1));
+#pragma unroll
+    for (int k = 0; k < kSegBatch; ++k)
+      if (base + k * kCutSegThreads < i1) use(base + k * kCutSegThreads, x[k]);
+  }
+}
+
 template <bool MOD>
 __device__ __forceinline__ uint64_t segment_probs(const float* __restrict__ z, const RowStat& st, float inv_t, int i0,
                                                   int i1, float* __restrict__ pr) {
   uint64_t w = 0;
-  for (int i = i0 + static_cast<int>(threadIdx.x); i < i1; i += kCutSegThreads) {
-    const float x = prob_final<MOD>(z[i], st, inv_t, i);
+  for_segment(i0, i1, [&](int i) { return z[i]; }, [&](int i, float zi) {
+    const float x = prob_final<MOD>(zi, st, inv_t, i);
     pr[i] = x;
     w += fixed_weight(x);
-  }
+  });
   return w;
 }
 
@@ -1270,6 +1268,20 @@ struct QLogits {
   __device__ Row row(int r) const { return Row{z + static_cast<size_t>(r) * V, st[r], inv_t}; }
 };
 
+// The same before the row statistics are stored: merged from the wave
+// partials of cut_part_kernel (unmodified rows).
+struct QParts {
+  const float* z;
+  char* cut;
+  size_t cut_bytes;
+  float inv_t;
+  int V;
+  typedef QLogits::Row Row;
+  __device__ Row row(int r) const {
+    return Row{z + static_cast<size_t>(r) * V, stat_of_parts(cut_row(cut, cut_bytes, r).part), inv_t};
+  }
+};
+
 __device__ __forceinline__ bool not_finite(float x) { return !(fabsf(x) < INFINITY); }
 
 // The final draw of one sequence: from (q - p)_+ if resid (falling back to
@@ -1302,10 +1314,11 @@ __device__ __forceinline__ int accept_draw(const Row& qr, const float* __restric
 // first rejected draft (K if none), bad = x~_a is out of range, nf = a value
 // the tests read or a target row of the sequence is non-finite, u = the
 // uniform of the final draw. Every lane of the wave returns the same values.
-// drafts[t] is x~_{t+1}. Lane t < K forms r_t and lane K u in one Philox
-// evaluation (~400 VALU instructions), which runs while the drafts load.
-template <class QS>
-__device__ __forceinline__ void accept_tests(const QS& qs, const float* __restrict__ p,
+// qr is lane t's target row, t <= K; drafts[t] is x~_{t+1}. Lane t < K forms
+// r_t and lane K u in one Philox evaluation (~400 VALU instructions), which
+// runs while the drafts load.
+template <class Row>
+__device__ __forceinline__ void accept_tests(const Row& qr, const float* __restrict__ p,
                                              const int32_t* __restrict__ dr, const float* __restrict__ unif,
                                              uint64_t seed, uint64_t loop, int K, int V, int b, int* a_out,
                                              bool* bad_out, bool* nf_out, float* u_out) {
@@ -1316,7 +1329,6 @@ __device__ __forceinline__ void accept_tests(const QS& qs, const float* __restri
     r = unif ? unif[b * (K + 1) + lane] : philox_uniform(seed, loop, lane < K ? 1 : 2, b, lane < K ? lane : 0);
   bool rejected = false, bad = false, nf = false;
   if (lane <= K) {
-    const typename QS::Row qr = qs.row(b * (K + 1) + lane);
     nf = qr.nonfinite();
     if (lane < K) {
       bad = x < 0 || x >= V;
@@ -1379,7 +1391,7 @@ __global__ __launch_bounds__(kSampleThreads) void accept_kernel(QS qs, const flo
     int a;
     bool bad, nf;
     float u;
-    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
+    accept_tests(qs.row(b * (K + 1) + min(tid, K)), p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
     if (tid == 0) {
       if (bad) atomicOr(err, kErrBadToken);
       s_a = a;
@@ -1456,7 +1468,7 @@ __global__ __launch_bounds__(kSampleThreads) void accept_probs_kernel(
     int a;
     bool bad, nf;
     float u;
-    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
+    accept_tests(qs.row(b * (K + 1) + min(tid, K)), p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
     if (tid == 0) {
       if (bad) atomicOr(err, kErrBadToken);
       s_a = a;
@@ -1535,9 +1547,9 @@ __global__ __launch_bounds__(kSampleThreads) void accept_probs_kernel(
 
 // ---------------------------------------------------------------------------
 // The verify step's accept / resample over several CUs (the same outcome as
-// accept_kernel). accept_part_kernel's work-groups take one segment of the
-// final draw's row each: every one runs the accept tests (K gathers) to find
-// that row, then adds its segment's residual weights (q - p)_+ and q
+// accept_kernel). verify_tail_kernel's accept work-groups take one segment of
+// the final draw's row each: every one runs the accept tests (K gathers) to
+// find that row, then adds its segment's residual weights (q - p)_+ and q
 // weights (the zero-residual fallback and the bonus draw) and flags a
 // non-finite value among them; accept_draw_kernel finds the segment that
 // holds the draw's threshold from the totals and scans only it. Integer sums
@@ -1550,42 +1562,86 @@ constexpr int kAccNf = 64, kAccHead = 128;
 static_assert(kAccNf >= kMaxRowSegments && kAccHead >= kAccNf + kMaxRowSegments && kAccHead + 3 <= kCutBuckets,
               "accept totals fit the row scratch");
 
-template <bool MOD, class Row>
-__device__ __forceinline__ void segment_accept_weights(const Row& qr, const float* __restrict__ prow, bool resid,
+template <bool MOD>
+__device__ __forceinline__ void segment_accept_weights(const QLogits::Row& qr, const float* __restrict__ prow, bool resid,
                                                        int i0, int i1, uint64_t* wr, uint64_t* wq, bool* nf) {
-  for (int i = i0 + static_cast<int>(threadIdx.x); i < i1; i += kCutSegThreads) {
-    const float xq = qr.template get<MOD>(i);
-    *nf |= not_finite(xq);
-    const uint64_t x = fixed_weight(xq);
+  for_segment(i0, i1, [&](int i) { return make_float2(qr.z[i], resid ? prow[i] : 0.f); }, [&](int i, float2 v) {
+    const float xq = prob_final<MOD>(v.x, qr.st, qr.inv_t, i);
+    *nf |= not_finite(xq) | not_finite(v.y);
+    const uint64_t x = fixed_weight(xq), y = fixed_weight(v.y);
     *wq += x;
-    if (resid) {
-      const float xp = prow[i];
-      *nf |= not_finite(xp);
-      const uint64_t y = fixed_weight(xp);
-      *wr += x > y ? x - y : 0;
-    }
-  }
+    *wr += x > y ? x - y : 0;
+  });
 }
 
-// Grid (segments, B), kCutSegThreads threads.
+// Probabilities of entries [i0, i1) of a row into pr.
+template <bool MOD>
+__device__ __forceinline__ void segment_export(const QLogits::Row& qr, int i0, int i1, float* __restrict__ pr) {
+  for_segment(i0, i1, [&](int i) { return qr.z[i]; },
+              [&](int i, float zi) { pr[i] = prob_final<MOD>(zi, qr.st, qr.inv_t, i); });
+}
+
+// Everything of the verify step's tail that needs a row's statistics but not
+// its draw: grid (segments, nexp + B), kCutSegThreads threads. Work-groups
+// (s, y < nexp) export segment s (eseg entries) of q row y; work-groups (s,
+// nexp + b) take segment s (seg entries) of sequence b's final draw. With QParts (unmodified rows at
+// temperature > 0) every work-group merges the statistics it needs from the
+// rows' partials, and those of segment 0 store them (for the draw) and raise
+// the flag of non-finite rows. 5 rows of 32000 exported and accepted: a
+// softmax of one work-group per row and the accept's two launches took 20.3 +
+// 8.8 + 7.9 us, the partials, this kernel and the draw 5.2 + 7.3 + 7.0; 144
+// rows (16 sequences) 27.4 + 10.3 + 10.0 and 11.0 + 26.0 + 9.2.
 template <class QS>
-__global__ __launch_bounds__(kCutSegThreads) void accept_part_kernel(QS qs, const float* __restrict__ p,
+__global__ __launch_bounds__(kCutSegThreads) void verify_tail_kernel(QS qs, const float* __restrict__ p,
                                                                      const int32_t* __restrict__ drafts, int dstride,
                                                                      int doff, const float* __restrict__ unif,
                                                                      uint64_t seed, uint64_t loop, int K, int V,
                                                                      char* __restrict__ cut, size_t cut_bytes,
-                                                                     int seg) {
+                                                                     int seg, int nseg, int nexp, int eseg,
+                                                                     float* __restrict__ probs,
+                                                                     RowStat* __restrict__ stats, int* err) {
+  constexpr bool kMerge = __is_same(QS, QParts);
   __shared__ int s_a, s_nf;
+  __shared__ RowStat s_st;
   __shared__ uint64_t s_r[kCutSegThreads / 64], s_q[kCutSegThreads / 64];   // per wave: residual, q totals
   __shared__ int s_wnf[kCutSegThreads / 64];                                  // per wave: a non-finite value
-  const int b = blockIdx.y, s = blockIdx.x, tid = threadIdx.x;
+  const int s = blockIdx.x, tid = threadIdx.x;
+  if (static_cast<int>(blockIdx.y) < nexp) {        // uniform: an export work-group
+    const int r = blockIdx.y;
+    const int i0 = s * eseg, i1 = min(V, i0 + eseg);
+    if (i0 >= i1) return;                           // export and accept rows have segments of their own
+    // One wave merges (16 steps of two exponentials, the larger part of the
+    // work-group's instructions if every wave did).
+    if (tid < 64) {
+      const RowStat st = qs.row(r).st;
+      if (tid == 0) s_st = st;
+    }
+    __syncthreads();
+    const QLogits::Row qr{qs.z + static_cast<size_t>(r) * V, s_st, qs.inv_t};
+    if (kMerge && s == 0 && tid == 0 && qr.nonfinite()) atomicOr(err, kErrNonFinite);
+    if (!probs) return;
+    float* pr = probs + static_cast<size_t>(r) * V;
+    if (qr.modified()) segment_export<true>(qr, i0, i1, pr);
+    else segment_export<false>(qr, i0, i1, pr);
+    return;
+  }
+  if (s >= nseg) return;
+  const int i0 = s * seg, i1 = min(V, i0 + seg);
+  const int b = blockIdx.y - nexp;
   const int32_t* dr = drafts + static_cast<size_t>(b) * dstride + doff;
   const CutRowScratch cs = cut_row(cut, cut_bytes, b);
   if (tid < 64) {
     int a;
     bool bad, nf;
     float u;
-    accept_tests(qs, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
+    const int r = b * (K + 1) + min(tid, K);
+    const QLogits::Row qr = qs.row(r);
+    if (kMerge && s == 0 && tid <= K) {
+      stats[r] = qr.st;
+      if (qr.nonfinite()) atomicOr(err, kErrNonFinite);
+    }
+    accept_tests(qr, p, dr, unif, seed, loop, K, V, b, &a, &bad, &nf, &u);
+    if (tid == a) s_st = qr.st;
     if (tid == 0) {
       s_a = a;
       s_nf = nf;
@@ -1602,9 +1658,8 @@ __global__ __launch_bounds__(kCutSegThreads) void accept_part_kernel(QS qs, cons
   bool nf = false;
   if (!s_nf) {                                     // uniform: the tests' inputs were finite
     const bool resid = a < K;
-    const typename QS::Row qr = qs.row(b * (K + 1) + a);
+    const QLogits::Row qr{qs.z + (static_cast<size_t>(b) * (K + 1) + a) * V, s_st, qs.inv_t};
     const float* prow = p + (static_cast<size_t>(b) * K + (resid ? a : 0)) * V;
-    const int i0 = s * seg, i1 = min(V, i0 + seg);
     if (qr.modified())
       segment_accept_weights<true>(qr, prow, resid, i0, i1, &wr, &wq, &nf);
     else
@@ -1681,23 +1736,28 @@ __global__ __launch_bounds__(kCutSegThreads) void accept_draw_kernel(QS qs, cons
   const int mode = s_mode, sstar = s_seg;
   if (mode != -2 && sstar >= 0) {                 // uniform
     const typename QS::Row qr = qs.row(b * (K + 1) + a);
-    const float* prow = p + (static_cast<size_t>(b) * K + (resid ? a : 0)) * V;
+    // (without a residual p is not used, and may be NULL)
+    const float* prow = mode == 0 ? qr.z : p + (static_cast<size_t>(b) * K + a) * V;
     const bool mod = qr.modified();
-    auto wt = [&](int i) -> uint64_t {
-      const uint64_t x = fixed_weight(mod ? qr.template get<true>(i) : qr.template get<false>(i));
-      if (mode == 0) return x;
-      const uint64_t y = fixed_weight(prow[i]);
-      return x > y ? x - y : 0;
-    };
     const uint64_t thr = s_thr;
     const int i0 = sstar * seg, i1 = min(V, i0 + seg);
     uint64_t run = s_off;
     for (int base = i0; base < i1; base += kCutSegThreads * kDrawPer) {
       uint64_t w[kDrawPer], lt = 0;
+      float zq[kDrawPer], xp[kDrawPer];
       const int c0 = base + kDrawPer * tid;
 #pragma unroll
+      for (int k = 0; k < kDrawPer; ++k) {         // loads first, none behind a branch
+        const int i = min(c0 + k, i1 - 1);
+        zq[k] = qr.z[i];
+        xp[k] = prow[i];
+      }
+#pragma unroll
       for (int k = 0; k < kDrawPer; ++k) {
-        w[k] = c0 + k < i1 ? wt(c0 + k) : 0;
+        const uint64_t x = fixed_weight(mod ? prob_final<true>(zq[k], qr.st, qr.inv_t, c0 + k)
+                                            : prob_final<false>(zq[k], qr.st, qr.inv_t, c0 + k));
+        const uint64_t y = mode == 0 ? 0 : fixed_weight(xp[k]);
+        w[k] = c0 + k < i1 && x > y ? x - y : 0;
         lt += w[k];
       }
       uint64_t total;
@@ -1832,17 +1892,8 @@ static hipError_t cut_rows(const float* logits, int rows, int rstride, int roff,
 }
 
 hipError_t launch_row_softmax(const float* logits, int rows, int V, float temperature, int top_k, float top_p,
-                              void* stats, float* probs, char* cut, int* err, hipStream_t st) {
+                              void* stats, float* probs, int* err, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
-  if (cut && stats && modifiers_active(temperature, top_k, top_p, V) && V <= modifier_max_vocab()) {
-    int seg = 0, nseg = 0;
-    RowStat* rs = reinterpret_cast<RowStat*>(stats);
-    const hipError_t e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, rs, cut, err, &seg, &nseg, st);
-    if (e != hipSuccess || !probs) return e;
-    hipLaunchKernelGGL(cut_export_kernel, dim3(nseg, rows), dim3(kCutSegThreads), 0, st, logits, V, temperature, rs,
-                       probs, seg);
-    return hipGetLastError();
-  }
   size_t lds = 0;
   const hipError_t e = cutoff_lds(reinterpret_cast<const void*>(&row_softmax_kernel), temperature, top_k, top_p, V,
                                   &lds);
@@ -1869,26 +1920,56 @@ hipError_t launch_accept_probs(const float* p, const float* q, const int32_t* dr
   return hipGetLastError();
 }
 
-hipError_t launch_accept_logits(const float* p, const float* logits, const void* stats, float temperature,
-                                const int32_t* tokens, const float* unif, uint64_t seed, uint64_t loop, int B,
-                                int K, int V, int32_t* out, int32_t* n_acc, char* cut, int* err, hipStream_t st) {
+hipError_t launch_verify_tail(const float* logits, int B, int K, int V, float temperature, int top_k, float top_p,
+                              void* stats, char* cut, float* probs, bool accept, const float* p,
+                              const int32_t* tokens, const float* unif, uint64_t seed, uint64_t loop, int32_t* out,
+                              int32_t* n_acc, int* err, hipStream_t st) {
+  const int rows = B * (K + 1);
   const float inv_t = temperature == 0.f ? 0.f : 1.0f / temperature;
-  const QLogits qs{logits, reinterpret_cast<const RowStat*>(stats), inv_t, V};
-  if (cut && V <= modifier_max_vocab()) {
-    int seg = 0, nseg = 0;
-    cut_segments(B, V, &seg, &nseg);
-    const size_t cut_bytes = cut_row_bytes(V);
-    hipLaunchKernelGGL(accept_part_kernel<QLogits>, dim3(nseg, B), dim3(kCutSegThreads), 0, st, qs, p, tokens, K + 1,
-                       1, unif, seed, loop, K, V, cut, cut_bytes, seg);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(accept_draw_kernel<QLogits>, dim3(B), dim3(kCutSegThreads), 0, st, qs, p, tokens, K + 1, 1,
-                       unif, seed, loop, K, V, static_cast<const char*>(cut), cut_bytes, nseg, seg, out, n_acc,
-                       err);
-    return hipGetLastError();
+  RowStat* rs = reinterpret_cast<RowStat*>(stats);
+  const QLogits qs{logits, rs, inv_t, V};
+  hipError_t e = hipSuccess;
+  // Greedy rows and rows past the partials' registers: statistics (and the
+  // export) by one work-group per row.
+  const bool whole = temperature == 0.f || V > modifier_max_vocab();
+  if (whole) {
+    e = launch_row_softmax(logits, rows, V, temperature, top_k, top_p, stats, probs, err, st);
+    if (e != hipSuccess || !accept) return e;
+    if (V > modifier_max_vocab()) {
+      hipLaunchKernelGGL(accept_kernel<QLogits>, dim3(B), dim3(kSampleThreads), 0, st, qs, p, tokens, K + 1, 1, unif,
+                         seed, loop, K, V, out, n_acc, err);
+      return hipGetLastError();
+    }
   }
-  hipLaunchKernelGGL(accept_kernel<QLogits>, dim3(B), dim3(kSampleThreads), 0, st, qs, p, tokens, K + 1, 1, unif,
-                     seed, loop, K, V, out, n_acc, err);
+  const size_t cut_bytes = cut_row_bytes(V);
+  const bool merge = !whole && !modifiers_active(temperature, top_k, top_p, V);
+  // Rows to export; without an accept stage unmodified rows still need their
+  // non-finite flags raised.
+  const int nexp = whole ? 0 : probs || (merge && !accept) ? rows : 0;
+  const int ny = nexp + (accept ? B : 0);
+  int seg = 0, nseg = 0;
+  if (!whole && !merge) {
+    e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, rs, cut, err, &seg, &nseg, st);
+    if (e != hipSuccess || ny == 0) return e;
+  }
+  cut_segments(B, V, &seg, &nseg);
+  // Export segments: about 2048 work-groups (8 per CU), at most 32 per row.
+  const int en = nexp ? std::max(1, std::min(kMaxRowSegments, 2048 / nexp)) : 1;
+  const int eseg = (V + en - 1) / en;
+  const int nx = std::max(accept ? nseg : 1, nexp ? en : 1);
+  if (merge) {
+    hipLaunchKernelGGL(cut_part_kernel, dim3(kStatWaves, rows), dim3(64), 0, st, logits, V, 1, 0, temperature, cut,
+                       cut_bytes);
+    hipLaunchKernelGGL(verify_tail_kernel<QParts>, dim3(nx, ny), dim3(kCutSegThreads), 0, st,
+                       QParts{logits, cut, cut_bytes, inv_t, V}, p, tokens, K + 1, 1, unif, seed, loop, K, V, cut,
+                       cut_bytes, seg, nseg, nexp, eseg, probs, rs, err);
+  } else {
+    hipLaunchKernelGGL(verify_tail_kernel<QLogits>, dim3(nx, ny), dim3(kCutSegThreads), 0, st, qs, p, tokens, K + 1,
+                       1, unif, seed, loop, K, V, cut, cut_bytes, seg, nseg, nexp, eseg, probs, rs, err);
+  }
+  if (accept)
+    hipLaunchKernelGGL(accept_draw_kernel<QLogits>, dim3(B), dim3(kCutSegThreads), 0, st, qs, p, tokens, K + 1, 1,
+                       unif, seed, loop, K, V, static_cast<const char*>(cut), cut_bytes, nseg, seg, out, n_acc, err);
   return hipGetLastError();
 }
 

@@ -481,12 +481,10 @@ sps_status verify_impl(sps_model_t target, sps_kv_t kv, const int32_t* tokens, i
   s = forward_impl(target, kv, tokens, K + 1, B, K + 1, 0, logits, base, ws, err, st);
   if (s != SPS_OK) return s;
   const int V = target->cfg.vocab;
-  SPS_HIP(sps::launch_row_softmax(logits, B * (K + 1), V, sampling.temperature, sampling.top_k, sampling.top_p,
-                                  stats, q_out, base + ws.cut, err, st));
-  if (acc)
-    SPS_HIP(sps::launch_accept_logits(acc->p_draft, logits, stats, sampling.temperature, tokens, acc->uniforms,
-                                      acc->rng.seed, acc->rng.loop, B, K, V, acc->out_tokens, acc->n_accepted,
-                                      base + ws.cut, err, st));
+  SPS_HIP(sps::launch_verify_tail(logits, B, K, V, sampling.temperature, sampling.top_k, sampling.top_p, stats,
+                                  base + ws.cut, q_out, acc != nullptr, acc ? acc->p_draft : nullptr, tokens,
+                                  acc ? acc->uniforms : nullptr, acc ? acc->rng.seed : 0, acc ? acc->rng.loop : 0,
+                                  acc ? acc->out_tokens : nullptr, acc ? acc->n_accepted : nullptr, err, st));
   return SPS_OK;
 }
 
@@ -586,7 +584,7 @@ sps_status sps_softmax(const float* logits, int32_t rows, int32_t V, sps_samplin
   int* err = device_error_ptr();
   if (!err) return SPS_E_HIP;
   SPS_HIP(sps::launch_row_softmax(logits, rows, V, sampling.temperature, sampling.top_k, sampling.top_p, nullptr,
-                                  probs, nullptr, err, as_stream(stream)));
+                                  probs, err, as_stream(stream)));
   return SPS_OK;
 }
 
