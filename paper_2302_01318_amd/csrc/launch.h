@@ -86,6 +86,10 @@ hipError_t launch_kv_copy(int dtype, int to_cache, void* kc, void* vc, int H, in
 // modifiers (top_k <= 0 or >= V: off; top_p >= 1: off), one work-group per row.
 hipError_t launch_row_softmax(const float* logits, int rows, int V, float temperature, int top_k, float top_p,
                               void* stats, float* probs, int* err, hipStream_t st);
+// sps_softmax: the probabilities alone, over several CUs per row where the
+// rows and the output allow it.
+hipError_t launch_softmax(const float* logits, int rows, int V, float temperature, int top_k, float top_p, float* probs,
+                          int* err, hipStream_t st);
 hipError_t launch_accept_probs(const float* p, const float* q, const int32_t* drafts,
                                const float* unif, uint64_t seed, uint64_t loop, int B, int K,
                                int V, int32_t* out, int32_t* n_acc, int* err, hipStream_t st);

@@ -567,6 +567,25 @@ __global__ __launch_bounds__(kSampleThreads) void row_softmax_kernel(const float
   if (probs) write_probs(z, V, st, inv_t, probs + static_cast<size_t>(row) * V);
 }
 
+// Unmodified rows with gridDim.x work-groups each: every one takes the whole
+// row's statistics (the bits of row_softmax_kernel) and exports one segment.
+// The row is read gridDim.x times from L2, which costs less than leaving the
+// export to one CU; the output must not overlap the logits.
+__global__ __launch_bounds__(kSampleThreads) void row_softmax_seg_kernel(const float* __restrict__ logits, int V,
+                                                                         float temperature,
+                                                                         float* __restrict__ probs, int seg, int* err) {
+  __shared__ float red[32];
+  __shared__ int ired[16];
+  const int row = blockIdx.y;
+  const float* z = logits + static_cast<size_t>(row) * V;
+  const RowStat st = row_stat(z, V, temperature, red, ired);
+  if (st.nonfinite && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(err, kErrNonFinite);
+  const float inv_t = temperature == 0.f ? 0.f : 1.0f / temperature;
+  float* pr = probs + static_cast<size_t>(row) * V;
+  const int i0 = blockIdx.x * seg, i1 = min(V, i0 + seg);
+  for (int i = i0 + static_cast<int>(threadIdx.x); i < i1; i += kSampleThreads) pr[i] = prob_of(z[i], st, inv_t, i);
+}
+
 // ---------------------------------------------------------------------------
 // The top-k / nucleus cut-off of the rows of a verify or draft step over
 // several CUs (one work-group per row is instruction-bound at ~290 VALU
@@ -599,9 +618,12 @@ struct CutRowScratch {
   CutPart* part;
   uint16_t* bid;
 };
+// (The scratch starts at the row's first 8-byte boundary: rows of a workspace
+// lie on one, output rows that serve as scratch need not.)
 __device__ __forceinline__ CutRowScratch cut_row(char* base, size_t row_bytes, int r) {
   constexpr size_t kHist = (static_cast<size_t>(kCutBuckets) * 2 * sizeof(uint64_t) + 255) & ~static_cast<size_t>(255);
   char* p = base + static_cast<size_t>(r) * row_bytes;
+  p += -reinterpret_cast<uintptr_t>(p) & 7;
   return CutRowScratch{reinterpret_cast<uint64_t*>(p), reinterpret_cast<uint64_t*>(p) + kCutBuckets,
                        reinterpret_cast<CutPart*>(p + kHist), reinterpret_cast<uint16_t*>(p + kHist + 256)};
 }
@@ -622,6 +644,11 @@ __device__ __forceinline__ RowStat stat_of_parts(const CutPart* __restrict__ par
   st.a = bad ? 0.f : mx;
   st.b = bad ? -1.f : sm;
   return st;
+}
+
+// Where row r's statistics go: the caller's array, or behind the row's bucket ids.
+__device__ __forceinline__ RowStat* cut_stat(RowStat* stats, const CutRowScratch& cs, int r, int V) {
+  return stats ? stats + r : reinterpret_cast<RowStat*>(cs.bid + (V + 3) / 4 * 4);
 }
 
 __device__ __forceinline__ const float* cut_logits(const float* logits, int r, int rstride, int roff, int V) {
@@ -659,7 +686,7 @@ __global__ __launch_bounds__(kCutSegThreads) void cut_hist_kernel(const float* _
   const RowStat st = stat_of_parts(cs.part);
   // The row's statistics as merged here go to stats[r]: the select reads these
   // bits rather than merging again, so its keys are the ones bucketed here.
-  if (s == 0 && threadIdx.x == 0) stats[r] = st;
+  if (s == 0 && threadIdx.x == 0) *cut_stat(stats, cs, r, V) = st;
   if (st.nonfinite) return;                        // uniform over the block
   for (int b = threadIdx.x; b < kCutBuckets; b += blockDim.x) {
     hn[b] = 0;
@@ -960,7 +987,8 @@ __global__ __launch_bounds__(kSampleThreads) void cut_select_kernel(const float*
                                                                     int rstride, int roff, float temperature,
                                                                     int top_k, float top_p,
                                                                     RowStat* __restrict__ stats,
-                                                                    char* __restrict__ cut, size_t cut_bytes, int* err) {
+                                                                    char* __restrict__ cut, size_t cut_bytes,
+                                                                    int copy_seg, int* err) {
   __shared__ CutScratch sc;
   __shared__ uint64_t sub_n[256], sub_w[256];
   extern __shared__ uint32_t s_rowkeys[];
@@ -971,9 +999,28 @@ __global__ __launch_bounds__(kSampleThreads) void cut_select_kernel(const float*
     sc.bins[b] = cs.n[b];
     sc.wbins[b] = cs.w[b];
   }
-  const RowStat base = stats[r];                   // merged by cut_hist_kernel
+  const RowStat base = *cut_stat(stats, cs, r, V); // merged by cut_hist_kernel
+  // The statistics for whoever exports the row: into the array or, where the
+  // scratch is the output row itself (no array), to the head of each of its
+  // segments, which only that segment's work-group reads and overwrites.
+  auto leave = [&](const RowStat& st) {
+    if (stats) {
+      if (threadIdx.x == 0) stats[r] = st;
+      return;
+    }
+    __syncthreads();                               // the scratch is read no more
+    const int s = threadIdx.x;
+    if (s * copy_seg < V) {
+      uint32_t w[sizeof(RowStat) / 4];
+      __builtin_memcpy(w, &st, sizeof(st));
+      uint32_t* head = reinterpret_cast<uint32_t*>(cut + static_cast<size_t>(r) * cut_bytes) + s * copy_seg;
+#pragma unroll
+      for (unsigned i = 0; i < sizeof(RowStat) / 4; ++i) head[i] = w[i];
+    }
+  };
   if (base.nonfinite) {                            // uniform: one-hot at index 0, never cut (as row_stat_final)
     if (threadIdx.x == 0) atomicOr(err, kErrNonFinite);
+    leave(base);
     return;
   }
   __syncthreads();
@@ -1001,7 +1048,29 @@ __global__ __launch_bounds__(kSampleThreads) void cut_select_kernel(const float*
   } else {
     row_cutoff(pf, V, top_k, top_p, st, sc, s_rowkeys);
   }
-  if (threadIdx.x == 0) stats[r] = st;
+  leave(st);
+}
+
+// The rows of a softmax with a cut, from the statistics cut_select_kernel
+// left at the head of every segment: grid (segments, rows).
+template <bool MOD>
+__device__ __forceinline__ void export_segment(const float* __restrict__ z, const RowStat& st, float inv_t, int i0,
+                                               int i1, float* __restrict__ pr);
+__global__ __launch_bounds__(kCutSegThreads) void cut_export_kernel(const float* __restrict__ logits, int V,
+                                                                    float temperature, float* __restrict__ probs,
+                                                                    int seg) {
+  const int r = blockIdx.y, i0 = blockIdx.x * seg, i1 = min(V, i0 + seg);
+  float* pr = probs + static_cast<size_t>(r) * V;
+  RowStat st;
+  uint32_t w[sizeof(RowStat) / 4];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(RowStat) / 4; ++i) w[i] = __float_as_uint(pr[i0 + i]);
+  __builtin_memcpy(&st, w, sizeof(st));
+  __syncthreads();                                 // every thread has it before any entry is written
+  const float* z = logits + static_cast<size_t>(r) * V;
+  const float inv_t = 1.0f / temperature;
+  if (row_modified(st)) export_segment<true>(z, st, inv_t, i0, i1, pr);
+  else export_segment<false>(z, st, inv_t, i0, i1, pr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1029,6 +1098,14 @@ __device__ __forceinline__ void for_segment(int i0, int i1, LD ld, USE use) {
     for (int k = 0; k < kSegBatch; ++k)
       if (base + k * kCutSegThreads < i1) use(base + k * kCutSegThreads, x[k]);
   }
+}
+
+// Probabilities of entries [i0, i1) of a row into pr.
+template <bool MOD>
+__device__ __forceinline__ void export_segment(const float* __restrict__ z, const RowStat& st, float inv_t, int i0,
+                                               int i1, float* __restrict__ pr) {
+  for_segment(i0, i1, [&](int i) { return z[i]; },
+              [&](int i, float zi) { pr[i] = prob_final<MOD>(zi, st, inv_t, i); });
 }
 
 template <bool MOD>
@@ -1574,13 +1651,6 @@ __device__ __forceinline__ void segment_accept_weights(const QLogits::Row& qr, c
   });
 }
 
-// Probabilities of entries [i0, i1) of a row into pr.
-template <bool MOD>
-__device__ __forceinline__ void segment_export(const QLogits::Row& qr, int i0, int i1, float* __restrict__ pr) {
-  for_segment(i0, i1, [&](int i) { return qr.z[i]; },
-              [&](int i, float zi) { pr[i] = prob_final<MOD>(zi, qr.st, qr.inv_t, i); });
-}
-
 // Everything of the verify step's tail that needs a row's statistics but not
 // its draw: grid (segments, nexp + B), kCutSegThreads threads. Work-groups
 // (s, y < nexp) export segment s (eseg entries) of q row y; work-groups (s,
@@ -1621,8 +1691,8 @@ __global__ __launch_bounds__(kCutSegThreads) void verify_tail_kernel(QS qs, cons
     if (kMerge && s == 0 && tid == 0 && qr.nonfinite()) atomicOr(err, kErrNonFinite);
     if (!probs) return;
     float* pr = probs + static_cast<size_t>(r) * V;
-    if (qr.modified()) segment_export<true>(qr, i0, i1, pr);
-    else segment_export<false>(qr, i0, i1, pr);
+    if (qr.modified()) export_segment<true>(qr.z, qr.st, qr.inv_t, i0, i1, pr);
+    else export_segment<false>(qr.z, qr.st, qr.inv_t, i0, i1, pr);
     return;
   }
   if (s >= nseg) return;
@@ -1871,10 +1941,10 @@ static hipError_t cutoff_lds(const void* kernel, float temperature, int top_k, f
 
 // The cut-off over several CUs for `rows` rows (logits row r rstride +
 // roff), their statistics into stats[0 .. rows).
+// (stats NULL: cut, rows of cut_bytes bytes, is the output the rows go to.)
 static hipError_t cut_rows(const float* logits, int rows, int rstride, int roff, int V, float temperature, int top_k,
-                           float top_p, RowStat* stats, char* cut, int* err, int* seg_out, int* nseg_out,
-                           hipStream_t st) {
-  const size_t cut_bytes = cut_row_bytes(V);
+                           float top_p, RowStat* stats, char* cut, size_t cut_bytes, int* err, int* seg_out,
+                           int* nseg_out, hipStream_t st) {
   int seg = 0, nseg = 0;
   cut_segments(rows, V, &seg, &nseg);
   size_t lds = 0;
@@ -1885,7 +1955,7 @@ static hipError_t cut_rows(const float* logits, int rows, int rstride, int roff,
   hipLaunchKernelGGL(cut_hist_kernel, dim3(nseg, rows), dim3(kCutSegThreads), 0, st, logits, V, rstride,
                      roff, temperature, stats, cut, cut_bytes, seg);
   hipLaunchKernelGGL(cut_select_kernel, dim3(rows), dim3(kSampleThreads), lds, st, logits, V, rstride, roff,
-                     temperature, top_k, top_p, stats, cut, cut_bytes, err);
+                     temperature, top_k, top_p, stats, cut, cut_bytes, seg, err);
   *seg_out = seg;
   *nseg_out = nseg;
   return hipGetLastError();
@@ -1901,6 +1971,43 @@ hipError_t launch_row_softmax(const float* logits, int rows, int V, float temper
   hipLaunchKernelGGL(row_softmax_kernel, dim3(rows), dim3(kSampleThreads), lds, st, logits, V, temperature, top_k,
                      top_p, reinterpret_cast<RowStat*>(stats), probs, err);
   return hipGetLastError();
+}
+
+hipError_t launch_softmax(const float* logits, int rows, int V, float temperature, int top_k, float top_p, float* probs,
+                          int* err, hipStream_t st) {
+  if (rows <= 0) return hipSuccess;
+  const size_t n = static_cast<size_t>(rows) * V;
+  const bool apart = reinterpret_cast<uintptr_t>(probs) >= reinterpret_cast<uintptr_t>(logits + n) ||
+                     reinterpret_cast<uintptr_t>(logits) >= reinterpret_cast<uintptr_t>(probs + n);
+  const size_t row_bytes = static_cast<size_t>(V) * 4;
+  // Several CUs per row, where the output does not overlap the logits (it is
+  // written before the row is read for the last time). Rows with a cut meet in
+  // the output itself, which holds their scratch until it is exported. Four
+  // launches against one work-group per row, nucleus 0.95: V = 32000, 1 / 5 /
+  // 20 / 64 rows 61.0 / 61.8 / 62.6 / 63.5 -> 27.1 / 29.1 / 36.8 / 43.0 us
+  // (144 rows: 64.9 and 64.2); V = 8000 27.4 / 27.5 / 27.8 / 28.1 -> 22.2 /
+  // 24.9 / 28.6 / 30.9, hence both bounds.
+  if (apart && modifiers_active(temperature, top_k, top_p, V)) {
+    if (row_bytes >= cut_row_bytes(V) + 512 && (rows <= 8 || (V >= 16384 && rows <= 64))) {
+      int seg = 0, nseg = 0;
+      const hipError_t e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, nullptr,
+                                    reinterpret_cast<char*>(probs), row_bytes, err, &seg, &nseg, st);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(cut_export_kernel, dim3(nseg, rows), dim3(kCutSegThreads), 0, st, logits, V, temperature,
+                         probs, seg);
+      return hipGetLastError();
+    }
+  } else if (apart && temperature > 0.f && V > kSampleThreads) {
+    // V = 32000: 1 / 5 / 64 rows 19.3 / 19.8 / 20.9 -> 12.7 / 13.0 / 17.5 us.
+    const int ns = std::min(8, kCUs / rows);
+    if (ns > 1) {
+      const int seg = (V + ns - 1) / ns;
+      hipLaunchKernelGGL(row_softmax_seg_kernel, dim3((V + seg - 1) / seg, rows), dim3(kSampleThreads), 0, st, logits,
+                         V, temperature, probs, seg, err);
+      return hipGetLastError();
+    }
+  }
+  return launch_row_softmax(logits, rows, V, temperature, top_k, top_p, nullptr, probs, err, st);
 }
 
 hipError_t launch_accept_probs(const float* p, const float* q, const int32_t* drafts, const float* unif,
@@ -1949,7 +2056,7 @@ hipError_t launch_verify_tail(const float* logits, int B, int K, int V, float te
   const int ny = nexp + (accept ? B : 0);
   int seg = 0, nseg = 0;
   if (!whole && !merge) {
-    e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, rs, cut, err, &seg, &nseg, st);
+    e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, rs, cut, cut_bytes, err, &seg, &nseg, st);
     if (e != hipSuccess || ny == 0) return e;
   }
   cut_segments(B, V, &seg, &nseg);
@@ -1984,7 +2091,7 @@ hipError_t launch_draft_sample(const float* logits, int Mps, int B, int V, float
     int seg = 0, nseg = 0;
     hipError_t e = hipSuccess;
     if (mod) {
-      e = cut_rows(logits, B, Mps, Mps - 1, V, temperature, top_k, top_p, rs, cut, err, &seg, &nseg, st);
+      e = cut_rows(logits, B, Mps, Mps - 1, V, temperature, top_k, top_p, rs, cut, cut_bytes, err, &seg, &nseg, st);
     } else {
       cut_segments(B, V, &seg, &nseg);
       hipLaunchKernelGGL(cut_part_kernel, dim3(kStatWaves, B), dim3(64), 0, st, logits, V, Mps, Mps - 1, temperature,

@@ -583,8 +583,8 @@ sps_status sps_softmax(const float* logits, int32_t rows, int32_t V, sps_samplin
   if (s != SPS_OK) return s;
   int* err = device_error_ptr();
   if (!err) return SPS_E_HIP;
-  SPS_HIP(sps::launch_row_softmax(logits, rows, V, sampling.temperature, sampling.top_k, sampling.top_p, nullptr,
-                                  probs, err, as_stream(stream)));
+  SPS_HIP(sps::launch_softmax(logits, rows, V, sampling.temperature, sampling.top_k, sampling.top_p, probs, err,
+                              as_stream(stream)));
   return SPS_OK;
 }
 

@@ -197,3 +197,31 @@ def test_draft_step_with_modifiers_v32000(sps, T, k, p):
             if k:
                 assert 1 <= (row > 0).sum() <= k
             assert row[toks[b, t + 1]] > 0
+
+
+@pytest.mark.parametrize("V", [1024, 1025, 4607, 4735, 4737, 5003, 16383, 16384, 32000, 32767, 32768])
+@pytest.mark.parametrize("rows", [1, 7, 9, 65])
+def test_softmax_over_several_cus_equals_in_place(sps, rows, V):
+    """sps_softmax into an output of its own may take several CUs per row (and
+    keep their scratch in that output); in place it never does. Same bits, for
+    ordinary, flat, one-hot, -Inf and non-finite rows, at the edges of the
+    dispatch and of the segments, with rows that start on any 4-byte boundary."""
+    g = torch.Generator(device="cuda").manual_seed(V + rows)
+    z = torch.randn(rows, V, generator=g, device="cuda") * 2
+    z[0, V // 2] += 40.0
+    if rows > 4:
+        z[1] = 0.25
+        z[2, 3:] = -float("inf")
+        z[3, V - 1] = float("nan")
+        z[4, ::2] = 1.0
+    for T, top_k, top_p in ((1.0, 0, 1.0), (0.8, 0, 0.95), (1.3, 40, 1.0), (0.5, 7, 0.6), (1.0, 0, 0.0)):
+        print("softmax rows", rows, "V", V, "T", T, "top_k", top_k, "top_p", top_p, flush=True)
+        buf = torch.full((rows * V + 8,), -1.0, device="cuda")
+        out = buf[3:3 + rows * V].view(rows, V)
+        sps.softmax(z, T, top_k, top_p, out=out)
+        want = z.clone()
+        sps.softmax(want, T, top_k, top_p, out=want)
+        assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+        assert (buf[:3] == -1).all() and (buf[3 + rows * V:] == -1).all()
+    flags = sps.device_error()
+    assert flags == (sps.DEV_NONFINITE if rows > 4 else 0)
