@@ -218,6 +218,16 @@ sps_status sps_forward(sps_model_t model, sps_kv_t kv, const int32_t* tokens, in
                        int32_t B, int32_t M, int32_t pos_offset, float* logits_out,
                        void* workspace, size_t ws_bytes, void* stream);
 
+/* sps_forward without logits for prompts, over longer chunks: M new tokens
+ * per sequence with B * M <= 160 (a chunk of more rows streams the weights
+ * fewer times per prompt). The workspace must hold
+ * sps_prefill_workspace_bytes(cfg, B, M, T_cap) bytes (0 for a request
+ * sps_prefill does not admit); one sized for more tokens also fits. */
+size_t sps_prefill_workspace_bytes(const sps_config* cfg, int32_t B, int32_t tokens, int32_t T_cap);
+sps_status sps_prefill(sps_model_t model, sps_kv_t kv, const int32_t* tokens, int32_t tok_stride,
+                       int32_t B, int32_t M, int32_t pos_offset, void* workspace, size_t ws_bytes,
+                       void* stream);
+
 /* Outputs of the fused accept / resample stage (Modified Rejection Sampling). */
 typedef struct {
   const float* p_draft; /* [B][K][V] fp32: the exact draft distributions the

@@ -125,6 +125,8 @@ __device__ __forceinline__ void attn_group(bool short_first, int* h, int* b, int
   *b = static_cast<int>(hb / H);
 }
 
+// (Mrow: rows of a sequence in q and the output, of which the launch takes Mps
+// from its pointers on.)
 // Grid (G, H, B), G = ceil(T_cap / (4 WP)), 4 waves. Wave w of position
 // group g covers positions 4 WP g + WP w .. + WP - 1 (WP = 32 or 64: one or
 // two blocks),
@@ -140,7 +142,7 @@ template <typename T, int DH, int QT, int WP, int KP = 1, bool NTL = false>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const T* __restrict__ q, const T* __restrict__ kc,
                                                            const T* __restrict__ vc,
                                                            const int32_t* __restrict__ lengths, int pos_offset,
-                                                           int Mps, int H, int T_cap, int NP, bool short_first,
+                                                           int Mps, int Mrow, int H, int T_cap, int NP, bool short_first,
                                                            float c_log2, float* __restrict__ part,
                                                            T* __restrict__ out, size_t oplane) {
   constexpr bool kMerge = QT == 1;
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const T* __restrict__
     const int qi = qt * 16 + r16;
 #pragma unroll
     for (int dt = 0; dt < DH / 32; ++dt)
-      qf[qt][dt] = qi < Mps ? load_frag(q + (static_cast<size_t>(b) * Mps + qi) * HD + h * DH + dt * 32 + grp * 8)
+      qf[qt][dt] = qi < Mps ? load_frag(q + (static_cast<size_t>(b) * Mrow + qi) * HD + h * DH + dt * 32 + grp * 8)
                             : Frag<T>::zero();
   }
   float m_run[QT], l_run[QT];
@@ -233,7 +235,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const T* __restrict__
         }
       }
       if (out) {                                   // the only group: normalised as attn_combine_kernel does
-        store_act(out, oplane, static_cast<size_t>(b * Mps + qi) * HD + h * DH + d, L == 0.f ? 0.f : acc / L);
+        store_act(out, oplane, static_cast<size_t>(b * Mrow + qi) * HD + h * DH + d, L == 0.f ? 0.f : acc / L);
         continue;
       }
       dst[qi * (DH + 2) + d] = acc;
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const T* __restrict__
 // covers `pp` positions.
 template <typename T, int DH>
 __global__ __launch_bounds__(DH) void attn_combine_kernel(const float* __restrict__ part, const int32_t* __restrict__ lengths,
-                                                          int pos_offset, int Mps, int H, int T_cap, int NP, int pp,
+                                                          int pos_offset, int Mps, int Mrow, int H, int T_cap, int NP, int pp,
                                                           float c_log2, T* __restrict__ o, size_t oplane) {
   const int row = blockIdx.x, h = blockIdx.y, d = threadIdx.x;
   const int b = row / Mps, qi = row % Mps;
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(DH) void attn_combine_kernel(const float* __restric
   }
   // L == 0: no visible position (nothing to average). A NaN among the
   // scores or values makes L or acc NaN, and the NaN is passed on.
-  store_act(o, oplane, static_cast<size_t>(row) * H * DH + h * DH + d, L == 0.f ? 0.f : acc / L);
+  store_act(o, oplane, (static_cast<size_t>(b) * Mrow + qi) * H * DH + h * DH + d, L == 0.f ? 0.f : acc / L);
 }
 
 
@@ -323,12 +325,12 @@ static hipError_t attn_decode_t(const void* q, const void* kc, const void* vc, c
   T* out = groups == 1 ? static_cast<T*>(o) : nullptr;
   hipLaunchKernelGGL((attn_partial_kernel<T, DH, 1, WP, KP, NTL>), dim3(groups, H, B), dim3(256), 0, st,
                      static_cast<const T*>(q), static_cast<const T*>(kc), static_cast<const T*>(vc), lengths,
-                     pos_offset, Mps, H, T_cap, groups, short_first_order(groups, H, B), c_log2, part, out,
+                     pos_offset, Mps, Mps, H, T_cap, groups, short_first_order(groups, H, B), c_log2, part, out,
                      oplane);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || out) return e;
   hipLaunchKernelGGL((attn_combine_kernel<T, DH>), dim3(B * Mps, H), dim3(DH), 0, st, part, lengths, pos_offset,
-                     Mps, H, T_cap, groups, 4 * WP, c_log2, static_cast<T*>(o), oplane);
+                     Mps, Mps, H, T_cap, groups, 4 * WP, c_log2, static_cast<T*>(o), oplane);
   return hipGetLastError();
 }
 
@@ -345,27 +347,35 @@ static hipError_t attn_t(const void* q, const void* kc, const void* vc, const in
       return attn_decode_t<T, DH, 64, 2, true>(q, kc, vc, lengths, pos_offset, B, Mps, H, T_cap, part, o, oplane, st);
     return attn_decode_t<T, DH, 64>(q, kc, vc, lengths, pos_offset, B, Mps, H, T_cap, part, o, oplane, st);
   }
-  // Prefill chunks: 2 or 4 query tiles, every wave writes its own partial.
+  // Prefill chunks: 64 queries at a time, in 2 or 4 query tiles (the chunk's
+  // keys are all in the cache, so later queries only see further), every wave
+  // writing its own partial.
   const float c_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(DH));
   const int groups = (T_cap + 4 * kWavePos - 1) / (4 * kWavePos);
   const dim3 grid(groups, H, B);
-  const T* qq = static_cast<const T*>(q);
   const T* kk = static_cast<const T*>(kc);
   const T* vv = static_cast<const T*>(vc);
   const int NP = attn_partials(T_cap);
-  if (Mps <= 32)
-    hipLaunchKernelGGL((attn_partial_kernel<T, DH, 2, kWavePos>), grid, dim3(256), 0, st, qq, kk, vv, lengths,
-                       pos_offset, Mps, H, T_cap, NP, short_first_order(groups, H, B), c_log2, part, static_cast<T*>(nullptr),
-                       oplane);
-  else
-    hipLaunchKernelGGL((attn_partial_kernel<T, DH, 4, kWavePos>), grid, dim3(256), 0, st, qq, kk, vv, lengths,
-                       pos_offset, Mps, H, T_cap, NP, short_first_order(groups, H, B), c_log2, part, static_cast<T*>(nullptr),
-                       oplane);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_combine_kernel<T, DH>), dim3(B * Mps, H), dim3(DH), 0, st, part, lengths, pos_offset,
-                     Mps, H, T_cap, NP, kWavePos, c_log2, static_cast<T*>(o), oplane);
-  return hipGetLastError();
+  for (int j = 0; j < Mps; j += kMaxTokensPerSeq) {
+    const int n = Mps - j < kMaxTokensPerSeq ? Mps - j : kMaxTokensPerSeq, at = pos_offset + j;
+    const T* qq = static_cast<const T*>(q) + static_cast<size_t>(j) * H * DH;
+    T* oo = static_cast<T*>(o) + static_cast<size_t>(j) * H * DH;
+    if (n <= 32)
+      hipLaunchKernelGGL((attn_partial_kernel<T, DH, 2, kWavePos>), grid, dim3(256), 0, st, qq, kk, vv, lengths, at, n,
+                         Mps, H, T_cap, NP, short_first_order(groups, H, B), c_log2, part, static_cast<T*>(nullptr),
+                         oplane);
+    else
+      hipLaunchKernelGGL((attn_partial_kernel<T, DH, 4, kWavePos>), grid, dim3(256), 0, st, qq, kk, vv, lengths, at, n,
+                         Mps, H, T_cap, NP, short_first_order(groups, H, B), c_log2, part, static_cast<T*>(nullptr),
+                         oplane);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((attn_combine_kernel<T, DH>), dim3(B * n, H), dim3(DH), 0, st, part, lengths, at, n, Mps, H,
+                       T_cap, NP, kWavePos, c_log2, oo, oplane);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_attention(int dtype, const void* q, const void* kc, const void* vc, const int32_t* lengths,

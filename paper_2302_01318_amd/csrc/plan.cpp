@@ -205,7 +205,7 @@ WsLayout make_ws(const Layout& L, int B, int Mps, int T_cap) {
   w.o = o; o = align256(o + M * L.HD * 4);                // attention output (activation format)
   w.q = o; o = align256(o + M * L.HD * L.es);             // rotated queries (model dtype)
   w.rope = o; o = align256(o + M * (L.DH / 2) * 8);       // rotary (cos, sin) per row and frequency
-  w.apart = o; o = align256(o + static_cast<size_t>(B) * L.H * NP * Mps * (L.DH + 2) * 4);
+  w.apart = o; o = align256(o + static_cast<size_t>(B) * L.H * NP * std::min(Mps, kMaxTokensPerSeq) * (L.DH + 2) * 4);
   w.act = o; o = align256(o + M * L.F * 4);               // FFN hidden (activation format)
   w.ss_a = o; o = align256(o + ng * M * 4);               // per-group sums of squares of h
   w.ss_b = o; o = align256(o + ng * M * 4);
@@ -222,6 +222,12 @@ size_t workspace_bytes(const sps_config* cfg, int B, int max_tokens_per_seq, int
   // No call runs more tokens per sequence or more rows than this.
   if (max_tokens_per_seq > kMaxTokensPerSeq || static_cast<long>(B) * max_tokens_per_seq > kMaxRows) return 0;
   return make_ws(make_layout(cfg), B, max_tokens_per_seq, T_cap).total;
+}
+
+size_t prefill_workspace_bytes(const sps_config* cfg, int B, int tokens, int T_cap) {
+  if (!valid_config(cfg) || B < 1 || tokens < 1 || T_cap < 32 || T_cap > kMaxTCap) return 0;
+  if (static_cast<long>(B) * tokens > kMaxRows) return 0;
+  return make_ws(make_layout(cfg), B, tokens, T_cap).total;
 }
 
 sps_status check_sampling(const sps_sampling& sp, int V) {

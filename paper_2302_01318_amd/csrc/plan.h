@@ -13,7 +13,7 @@
 namespace sps {
 
 // ---- limits of one call ------------------------------------------------
-constexpr int kMaxTokensPerSeq = 64;   // new tokens per sequence in one forward
+constexpr int kMaxTokensPerSeq = 64;   // new tokens per sequence in one forward (a prefill takes up to kMaxRows)
 constexpr int kMaxRows = 160;          // B * tokens per sequence in one forward
 constexpr int kMaxK = 63;              // lookahead
 constexpr int kMaxTCap = 1 << 22;      // KV capacity (positions): keeps grid extents and partial counts far inside their ranges
@@ -141,6 +141,9 @@ WsLayout make_ws(const Layout& L, int B, int Mps, int T_cap);
 
 // sps_workspace_bytes: 0 for an invalid request (see sps.h).
 size_t workspace_bytes(const sps_config* cfg, int B, int max_tokens_per_seq, int T_cap);
+
+// sps_prefill_workspace_bytes: 0 for an invalid request (see sps.h).
+size_t prefill_workspace_bytes(const sps_config* cfg, int B, int tokens, int T_cap);
 
 // Per-row scratch of the top-k / nucleus cut-off over several CUs: the
 // row's bucket histogram (counts, weights) and a bucket id per entry; 0

@@ -241,10 +241,10 @@ sps_status forward_impl(const sps_model_s* m, const sps_kv_s* kv, const int32_t*
 }
 
 sps_status check_forward_args(const sps_model_s* m, const sps_kv_s* kv, int B, int Mps, size_t ws_bytes,
-                              const void* ws, WsLayout* out) {
+                              const void* ws, WsLayout* out, int max_tokens = kMaxTokensPerSeq) {
   if (!m || !kv || !ws) return SPS_E_INVALID;
   if (B < 1 || Mps < 1) return SPS_E_INVALID;
-  if (Mps > kMaxTokensPerSeq || B * Mps > kMaxRows) return SPS_E_SHAPE;
+  if (Mps > max_tokens || static_cast<long>(B) * Mps > kMaxRows) return SPS_E_SHAPE;
   if (B != kv->B) return SPS_E_SHAPE;
   const sps_config& a = m->cfg;
   const sps_config& b = kv->cfg;
@@ -454,6 +454,22 @@ sps_status sps_forward(sps_model_t model, sps_kv_t kv, const int32_t* tokens, in
   if (!err) return SPS_E_HIP;
   return forward_impl(model, kv, tokens, tok_stride, B, M, pos_offset, logits_out, static_cast<char*>(workspace),
                       ws, err, as_stream(stream));
+}
+
+size_t sps_prefill_workspace_bytes(const sps_config* cfg, int32_t B, int32_t tokens, int32_t T_cap) {
+  return sps::prefill_workspace_bytes(cfg, B, tokens, T_cap);
+}
+
+sps_status sps_prefill(sps_model_t model, sps_kv_t kv, const int32_t* tokens, int32_t tok_stride, int32_t B, int32_t M,
+                       int32_t pos_offset, void* workspace, size_t ws_bytes, void* stream) {
+  WsLayout ws;
+  sps_status s = check_forward_args(model, kv, B, M, ws_bytes, workspace, &ws, kMaxRows);
+  if (s != SPS_OK) return s;
+  if (!tokens || tok_stride < M) return SPS_E_INVALID;
+  int* err = device_error_ptr();
+  if (!err) return SPS_E_HIP;
+  return forward_impl(model, kv, tokens, tok_stride, B, M, pos_offset, nullptr, static_cast<char*>(workspace), ws, err,
+                      as_stream(stream));
 }
 
 }  // extern "C"

@@ -27,6 +27,8 @@ TORCH_DTYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "fp8": torch.bfloat
 TENSOR_ID = {"embed": 0, "final_norm": 1, "unembed": 2, "attn_norm": 3, "wq": 4, "wk": 5, "wv": 6,
              "wo": 7, "ffn_norm": 8, "w1": 9, "w3": 10, "w2": 11}
 PURPOSE_DRAFT, PURPOSE_ACCEPT, PURPOSE_RESAMPLE = 0, 1, 2
+# Rows (sequences x tokens) of the Generator's prefill chunks.
+PREFILL_ROWS = 160
 DEV_BAD_TOKEN, DEV_EMPTY, DEV_CAPACITY, DEV_NONFINITE = 1, 2, 4, 8
 
 
@@ -76,6 +78,8 @@ _sig("sps_kv_write", c_int32, [P, c_int32, c_int32, c_int32, c_int32, P, P, P])
 _sig("sps_kv_read", c_int32, [P, c_int32, c_int32, c_int32, c_int32, P, P, P])
 _sig("sps_workspace_bytes", c_size_t, [ctypes.POINTER(Config), c_int32, c_int32, c_int32])
 _sig("sps_forward", c_int32, [P, P, P, c_int32, c_int32, c_int32, c_int32, P, P, c_size_t, P])
+_sig("sps_prefill_workspace_bytes", c_size_t, [ctypes.POINTER(Config), c_int32, c_int32, c_int32])
+_sig("sps_prefill", c_int32, [P, P, P, c_int32, c_int32, c_int32, c_int32, P, c_size_t, P])
 _sig("sps_verify_step", c_int32, [P, P, P, c_int32, c_int32, Sampling, P, P, ctypes.POINTER(AcceptIO), P,
                                   c_size_t, P])
 _sig("sps_verify_step_noalloc", c_int32, [P, P, P, c_int32, c_int32, Sampling, P, P, ctypes.POINTER(AcceptIO), P])
@@ -95,7 +99,7 @@ _sig("sps_profile_gemm_end", c_int32, [ctypes.POINTER(c_float), ctypes.POINTER(c
 
 EXPORTS = ["sps_status_string", "sps_abi_version", "sps_weight_bytes", "sps_pack_weight",
            "sps_model_create", "sps_model_destroy", "sps_kv_bytes", "sps_kv_create", "sps_kv_destroy",
-           "sps_kv_write", "sps_kv_read", "sps_workspace_bytes", "sps_forward", "sps_verify_step",
+           "sps_kv_write", "sps_kv_read", "sps_workspace_bytes", "sps_forward", "sps_prefill_workspace_bytes", "sps_prefill", "sps_verify_step",
            "sps_accept_resample", "sps_draft_step", "sps_commit", "sps_philox_uniforms", "sps_softmax",
            "sps_device_error", "sps_profile_gemm_begin", "sps_profile_gemm_end",
            "sps_stream_read", "sps_fp8_decode", "sps_weight_slot", "sps_verify_step_noalloc"]
@@ -209,10 +213,14 @@ class KVCache:
         self.handle = None
 
 
-def workspace(shape, B, max_tokens_per_seq, T_cap, device="cuda"):
+def workspace(shape, B, max_tokens_per_seq, T_cap, device="cuda", prefill_tokens=0):
+    """Scratch for forwards, verify and draft steps of up to max_tokens_per_seq
+    new tokens per sequence and, with prefill_tokens, for prefill() of that many."""
     n = lib.sps_workspace_bytes(ctypes.byref(config_of(shape)), B, max_tokens_per_seq, T_cap)
     if n == 0:
         raise SPSError(2, "sps_workspace_bytes")
+    if prefill_tokens:
+        n = max(n, lib.sps_prefill_workspace_bytes(ctypes.byref(config_of(shape)), B, prefill_tokens, T_cap))
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 
@@ -355,14 +363,16 @@ class Generator:
             raise ValueError("draft vocabulary %d differs from the target's %d"
                              % (draft.shape.vocab, target.shape.vocab))
         self.target, self.draft, self.B, self.K, self.T_cap = target, draft, B, K, T_cap
-        self.chunk = max(1, min(prefill_chunk, 160 // B, 64))
-        mps = max(self.chunk, K + 1, 2)
+        # Tokens per sequence of a prefill chunk: prefill_chunk up to the 64 of
+        # a forward, and from there (the default) what fits a prefill's rows.
+        self.chunk = max(1, min(prefill_chunk if prefill_chunk < 64 else PREFILL_ROWS // B, 160 // B))
+        mps = max(min(self.chunk, 64), K + 1, 2)
         self.lengths = torch.zeros(B, dtype=torch.int32, device=device)
         self.kv_t = KVCache(target.shape, B, T_cap, self.lengths, device)
-        self.ws_t = workspace(target.shape, B, mps, T_cap, device)
+        self.ws_t = workspace(target.shape, B, mps, T_cap, device, self.chunk)
         if draft is not None:
             self.kv_d = KVCache(draft.shape, B, T_cap, self.lengths, device)
-            self.ws_d = workspace(draft.shape, B, mps, T_cap, device)
+            self.ws_d = workspace(draft.shape, B, mps, T_cap, device, self.chunk)
         V = target.shape.vocab
         self.ctx = torch.zeros((B, 2), dtype=torch.int32, device=device)
         self.tokens = torch.zeros((B, K + 1), dtype=torch.int32, device=device)
@@ -381,8 +391,8 @@ class Generator:
             view = prompt[:, c0:]
             for model, kv, ws in ((self.target, self.kv_t, self.ws_t),) + \
                     (((self.draft, self.kv_d, self.ws_d),) if self.draft is not None else ()):
-                check(lib.sps_forward(model.handle, kv.handle, c_void_p(view.data_ptr()), Pn, B, n, c0, None,
-                                      _ptr(ws), ws.numel(), _stream()), "sps_forward(prefill)")
+                check(lib.sps_prefill(model.handle, kv.handle, c_void_p(view.data_ptr()), Pn, B, n, c0, _ptr(ws),
+                                      ws.numel(), _stream()), "sps_prefill")
         self.lengths.fill_(Pn - 1)
         self.ctx.copy_(prompt[:, Pn - 2:Pn])
 

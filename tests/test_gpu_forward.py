@@ -11,6 +11,8 @@ cache lengths; the full-width 7B- and 70B-shaped layers run in exactly the
 launch configuration of the benchmarked step (the per-layer kernels do not
 depend on the number of layers).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -153,6 +155,40 @@ def test_prefill_chunk_parity(sps):
     torch.cuda.synchronize()
     want = om.forward_cached(spec_of(shape), W, ocache, toks, np.array([10, 30]))
     assert np.abs(logits.cpu().numpy() - want).max() <= 2e-2
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("B,M", [(1, 65), (1, 96), (1, 97), (1, 129), (1, 160), (2, 80), (3, 53)])
+def test_long_prefill_chunk_parity(sps, dtype, tol, B, M):
+    """sps_prefill over chunks past a forward's 64 tokens (queries in groups of
+    64, the last of 1 to 64): the caches it leaves against the oracle's, over a
+    ragged prior context. Keys and values in the model dtype differ by a
+    rounding of the last bit at most now and then (tol as for logits)."""
+    shape = SMALL.with_(ffn="swiglu", dtype=dtype)
+    print("long prefill", dtype, B, M, flush=True)
+    gm, W = build_pair(shape, 8)
+    T = 224
+    prior = [40 - 13 * b for b in range(B)]
+    kv = sps.KVCache(shape, B, T)
+    ocache = new_cache(shape, B, T)
+    install_prior(shape, kv, ocache, 9, prior)
+    toks = synth.tokens(10, B, M, shape.vocab)
+    n = sps.lib.sps_prefill_workspace_bytes(ctypes.byref(kv.cfg), B, M, T)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    t = torch.from_numpy(toks).cuda()
+    call = lambda m, size: sps.lib.sps_prefill(gm.handle, kv.handle, t.data_ptr(), M, B, m, 0, ws.data_ptr(), size, None)  # noqa: E731
+    assert call(M, n - 1) == 3 and call(160 // B + 1, n) == 2
+    torch.cuda.synchronize()
+    assert call(M, n) == 0
+    torch.cuda.synchronize()
+    om.forward_cached(spec_of(shape), W, ocache, toks, np.array(prior))
+    for layer in range(shape.n_layers):
+        for b in range(B):
+            k, v = kv.read(layer, b, 0, prior[b] + M)
+            for got, name in ((k, "k"), (v, "v")):
+                want = ocache[name][layer, b, :, :prior[b] + M]
+                assert np.abs(got.double().cpu().numpy() - want).max() <= tol * max(1.0, np.abs(want).max())
+    assert sps.device_error() == 0
 
 
 def test_capacity_overflow_is_flagged(sps):
