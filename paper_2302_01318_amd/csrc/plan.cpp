@@ -205,7 +205,7 @@ WsLayout make_ws(const Layout& L, int B, int Mps, int T_cap) {
   w.o = o; o = align256(o + M * L.HD * 4);                // attention output (activation format)
   w.q = o; o = align256(o + M * L.HD * L.es);             // rotated queries (model dtype)
   w.rope = o; o = align256(o + M * (L.DH / 2) * 8);       // rotary (cos, sin) per row and frequency
-  w.apart = o; o = align256(o + static_cast<size_t>(B) * L.H * NP * std::min(Mps, kMaxTokensPerSeq) * (L.DH + 2) * 4);
+  w.apart = o; o = align256(o + static_cast<size_t>(B) * L.H * NP * Mps * (L.DH + 2) * 4);
   w.act = o; o = align256(o + M * L.F * 4);               // FFN hidden (activation format)
   w.ss_a = o; o = align256(o + ng * M * 4);               // per-group sums of squares of h
   w.ss_b = o; o = align256(o + ng * M * 4);
