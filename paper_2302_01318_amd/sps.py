@@ -29,6 +29,7 @@ TENSOR_ID = {"embed": 0, "final_norm": 1, "unembed": 2, "attn_norm": 3, "wq": 4,
 PURPOSE_DRAFT, PURPOSE_ACCEPT, PURPOSE_RESAMPLE = 0, 1, 2
 # Rows (sequences x tokens) of the Generator's prefill chunks.
 PREFILL_ROWS = 160
+PREFILL_BYTES = 2 << 30
 DEV_BAD_TOKEN, DEV_EMPTY, DEV_CAPACITY, DEV_NONFINITE = 1, 2, 4, 8
 
 
@@ -364,8 +365,15 @@ class Generator:
                              % (draft.shape.vocab, target.shape.vocab))
         self.target, self.draft, self.B, self.K, self.T_cap = target, draft, B, K, T_cap
         # Tokens per sequence of a prefill chunk: prefill_chunk up to the 64 of
-        # a forward, and from there (the default) what fits a prefill's rows.
-        self.chunk = max(1, min(prefill_chunk if prefill_chunk < 64 else PREFILL_ROWS // B, 160 // B))
+        # a forward, and from there (the default) what fits a prefill's rows,
+        # unless the attention partials of so many rows over a very long cache
+        # would take more than PREFILL_BYTES.
+        self.chunk = max(1, min(prefill_chunk, 160 // B, 64))
+        if prefill_chunk >= 64:
+            rows = PREFILL_ROWS // B
+            if max(lib.sps_prefill_workspace_bytes(ctypes.byref(config_of(m.shape)), B, max(rows, 1), T_cap)
+                   for m in (target, draft) if m is not None) <= PREFILL_BYTES:
+                self.chunk = max(self.chunk, rows)
         mps = max(min(self.chunk, 64), K + 1, 2)
         self.lengths = torch.zeros(B, dtype=torch.int32, device=device)
         self.kv_t = KVCache(target.shape, B, T_cap, self.lengths, device)
