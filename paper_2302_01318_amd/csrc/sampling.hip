@@ -64,11 +64,17 @@ struct RowStat {
 };
 static_assert(sizeof(RowStat) == kRowStatBytes, "workspace row statistics");
 
-// Probability of entry i of a row. The same expression (no contraction) is
-// used wherever q or p is materialised, so exported probabilities and the
-// values the accept test sees are identical bit for bit.
+// The row arithmetic below is inlined at many places whose results must be
+// the same bits (exported probabilities, the values the accept test sees, the
+// keys of the cut-off). The compiler contracts a multiply and an add as it
+// finds them, at each place on its own, and the __f*_rn functions are plain
+// operators to it, so every fused operation is written as one and the rest
+// stands under contract(off).
+
+// Probability of entry i of a row: the expression used wherever q or p is
+// materialised.
 __device__ __forceinline__ float prob_of(float z, RowStat st, float inv_t, int i) {
-  const float t = __fsub_rn(__fmul_rn(z, inv_t), st.a);
+  const float t = __builtin_fmaf(z, inv_t, -st.a);
   const float v = __fdiv_rn(expf(t), st.b);
   const float g = i == __float2int_rz(st.a) ? 1.f : 0.f;        // greedy row: one-hot at the arg-max
   return st.b < 0.f ? g : v;
@@ -107,6 +113,7 @@ struct SoftPart {
 };
 __device__ __forceinline__ SoftPart thread_soft_part(const float* __restrict__ z, int V, float inv_t, unsigned t,
                                                      unsigned nt) {
+#pragma clang fp contract(off)
   SoftPart p{-INFINITY, 0.f, false};
   float x[kPerLane];
 #pragma unroll
@@ -114,7 +121,7 @@ __device__ __forceinline__ SoftPart thread_soft_part(const float* __restrict__ z
     x[k] = z[min(t + k * nt, static_cast<unsigned>(V - 1))];
 #pragma unroll
   for (int k = 0; k < kPerLane; ++k) {
-    x[k] = t + k * nt < static_cast<unsigned>(V) ? __fmul_rn(x[k], inv_t) : -INFINITY;
+    x[k] = t + k * nt < static_cast<unsigned>(V) ? x[k] * inv_t : -INFINITY;
     p.bad |= !(x[k] < INFINITY);
     p.m = fmaxf(p.m, x[k]);
   }
@@ -124,13 +131,11 @@ __device__ __forceinline__ SoftPart thread_soft_part(const float* __restrict__ z
   }
   return p;
 }
-// (Explicit roundings: a contracted multiply-add could be formed differently
-// where the merge is inlined, and the partials' consumers must reproduce
-// row_stat's bits.)
 __device__ __forceinline__ void soft_merge(float& m, float& s2, float om, float os) {
+#pragma clang fp contract(off)
   const float nm = fmaxf(m, om);
   if (nm == -INFINITY) return;
-  s2 = __fadd_rn(__fmul_rn(s2, expf(m - nm)), __fmul_rn(os, expf(om - nm)));
+  s2 = __builtin_fmaf(os, expf(om - nm), s2 * expf(m - nm));
   m = nm;
 }
 __device__ __forceinline__ void wave_soft_merge(float& m, float& s2) {
@@ -144,6 +149,7 @@ __device__ __forceinline__ void wave_soft_merge(float& m, float& s2) {
 // red: __shared__ float[32], ired: __shared__ int[16].
 __device__ __forceinline__ RowStat row_stat(const float* __restrict__ z, int V, float temperature, float* red,
                                           int* ired) {
+#pragma clang fp contract(off)
   RowStat st;
   st.s = 0.f;
   st.nonfinite = 0;
@@ -187,10 +193,10 @@ __device__ __forceinline__ RowStat row_stat(const float* __restrict__ z, int V, 
     bad = p.bad;
   } else {
     for (int i = threadIdx.x; i < V; i += blockDim.x) {
-      const float x = __fmul_rn(z[i], inv_t);
+      const float x = z[i] * inv_t;
       bad |= !(x < INFINITY);
       if (x > mx) {
-        sm = sm * expf(mx - x) + 1.f;
+        sm = __builtin_fmaf(sm, expf(mx - x), 1.f);
         mx = x;
       } else if (x > -INFINITY) {
         sm += expf(x - mx);

@@ -160,6 +160,46 @@ def test_verify_accept_at_large_batch(sps, B, K):
     np.testing.assert_array_equal(nacc2, nacc)
 
 
+@pytest.mark.parametrize("V", [1024, 32000])
+@pytest.mark.parametrize("T", [1.0, 0.8, 1.3])
+def test_verify_accepts_against_the_exported_bits(sps, V, T):
+    """The q rows a verify step exports are the bits its accept tests use:
+    over 160 rows they equal sps.softmax of the exported logits bit for bit,
+    and with r = 1/2 a draft probability of 2 q(x) is rejected (r p < q is
+    false at equality) where 2 nextafter(q(x), 0) is accepted."""
+    shape = configs.ModelShape("v%d" % V, 128, 1, 2, 64, 256, V, "gelu", "bf16")
+    B, K, T_cap = 40, 3, 64
+    print("exported bits V", V, "T", T, flush=True)
+    gm = sps.Model(shape, synth.weights(shape, 51, 0.2))
+    kv = sps.KVCache(shape, B, T_cap)
+    kv.buf.zero_()
+    kv.lengths.fill_(8)
+    toks = cuda(synth.tokens(52, B, K + 1, V), torch.int32)
+    ws = sps.workspace(shape, B, K + 1, T_cap)
+    unif = torch.full((B, K + 1), 0.5, device="cuda")
+    x = toks[:, 1:].long()[..., None]
+
+    def run(p):
+        logits = torch.empty((B, K + 1, V), device="cuda")
+        q = torch.empty_like(logits)
+        out = torch.empty((B, K + 1), dtype=torch.int32, device="cuda")
+        nacc = torch.empty(B, dtype=torch.int32, device="cuda")
+        sps.verify_step(gm, kv, toks, K, T, ws, logits=logits, q=q, p_draft=p, uniforms=unif, out_tokens=out,
+                        n_accepted=nacc)
+        torch.cuda.synchronize()
+        assert sps.device_error() == 0
+        return logits, q, nacc
+
+    logits, q, _ = run(torch.zeros((B, K, V), device="cuda"))
+    assert int((q.view(torch.int32) != sps.softmax(logits, T).view(torch.int32)).sum()) == 0
+    qx = q[:, :K].gather(2, x)
+    assert (qx > 0).all()
+    for want, px in ((0, 2 * qx), (K, 2 * torch.nextafter(qx, torch.zeros_like(qx)))):
+        _, q2, nacc = run(torch.zeros((B, K, V), device="cuda").scatter_(2, x, px))
+        assert int((q2.view(torch.int32) != q.view(torch.int32)).sum()) == 0
+        assert nacc.tolist() == [want] * B
+
+
 def test_vocabulary_past_the_multi_cu_sampling(sps):
     """A 50257-token vocabulary, past the 32768 entries the multi-CU sampling
     paths take (rows this long go through the one-work-group kernels, whose
