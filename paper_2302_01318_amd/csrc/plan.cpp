@@ -185,8 +185,11 @@ size_t forward_part_bytes(const Layout& L, int M) {
 
 size_t cut_row_bytes(int V) {
   if (V > modifier_max_vocab()) return 0;
-  // histogram, 16 softmax partials (256 bytes), bucket ids
-  return align256(static_cast<size_t>(kCutBuckets) * 2 * sizeof(uint64_t)) + 256 + align256(static_cast<size_t>(V) * 2);
+  return align256(kCutIdsOffset + static_cast<size_t>(V) * 2);
+}
+
+bool cut_fits_output(int V) {
+  return V <= modifier_max_vocab() && static_cast<size_t>(V) * 4 >= cut_row_bytes(V) + 512;
 }
 
 WsLayout make_ws(const Layout& L, int B, int Mps, int T_cap) {

@@ -146,9 +146,20 @@ size_t workspace_bytes(const sps_config* cfg, int B, int max_tokens_per_seq, int
 size_t prefill_workspace_bytes(const sps_config* cfg, int B, int tokens, int T_cap);
 
 // Per-row scratch of the top-k / nucleus cut-off over several CUs: the
-// row's bucket histogram (counts, weights) and a bucket id per entry; 0
-// where the vocabulary is past what the cut-off handles.
+// row's bucket histogram (counts, then weights, uint64), 256 bytes of softmax
+// partials, a 16-bit bucket id per entry and, where the caller has no array
+// for them, the row's statistics. It starts at the row's first kCutAlign-byte
+// boundary (the ids are read in vectors of that size): rows of a workspace lie
+// on one, the output rows that sps_softmax uses as scratch need not.
+constexpr size_t kCutAlign = 16;
+constexpr size_t kCutPartOffset = (static_cast<size_t>(kCutBuckets) * 2 * 8 + 255) / 256 * 256;
+constexpr size_t kCutIdsOffset = kCutPartOffset + 256;
+constexpr size_t cut_row_shift(uintptr_t row) { return (kCutAlign - row % kCutAlign) % kCutAlign; }
+constexpr size_t cut_stat_offset(int V) { return kCutIdsOffset + (static_cast<size_t>(V) + 3) / 4 * 8; }
+// Bytes of a row's scratch in a workspace; 0 where the vocabulary is past what the cut-off handles.
 size_t cut_row_bytes(int V);
+// Whether rows of V fp32 outputs hold that scratch wherever they start.
+bool cut_fits_output(int V);
 
 // Segments of a row for the sampling kernels that take one segment per
 // work-group (the cut-off's histogram, the draft export): about 512

@@ -609,9 +609,7 @@ __global__ __launch_bounds__(kSampleThreads) void row_softmax_seg_kernel(const f
 // Row r of a launch is logits row r rstride + roff.
 // ---------------------------------------------------------------------------
 
-// Per-row scratch (cut_row_bytes(V) bytes): bucket counts, bucket weights,
-// the softmax partials of the row_stat waves, then a 16-bit bucket id per
-// entry.
+// Per-row scratch (its layout: plan.h).
 struct CutPart {
   float m, s;
   uint32_t bad, pad;
@@ -624,14 +622,11 @@ struct CutRowScratch {
   CutPart* part;
   uint16_t* bid;
 };
-// (The scratch starts at the row's first 8-byte boundary: rows of a workspace
-// lie on one, output rows that serve as scratch need not.)
 __device__ __forceinline__ CutRowScratch cut_row(char* base, size_t row_bytes, int r) {
-  constexpr size_t kHist = (static_cast<size_t>(kCutBuckets) * 2 * sizeof(uint64_t) + 255) & ~static_cast<size_t>(255);
   char* p = base + static_cast<size_t>(r) * row_bytes;
-  p += -reinterpret_cast<uintptr_t>(p) & 7;
+  p += cut_row_shift(reinterpret_cast<uintptr_t>(p));
   return CutRowScratch{reinterpret_cast<uint64_t*>(p), reinterpret_cast<uint64_t*>(p) + kCutBuckets,
-                       reinterpret_cast<CutPart*>(p + kHist), reinterpret_cast<uint16_t*>(p + kHist + 256)};
+                       reinterpret_cast<CutPart*>(p + kCutPartOffset), reinterpret_cast<uint16_t*>(p + kCutIdsOffset)};
 }
 
 // Row statistics from the wave partials, merged in wave order as row_stat
@@ -654,7 +649,8 @@ __device__ __forceinline__ RowStat stat_of_parts(const CutPart* __restrict__ par
 
 // Where row r's statistics go: the caller's array, or behind the row's bucket ids.
 __device__ __forceinline__ RowStat* cut_stat(RowStat* stats, const CutRowScratch& cs, int r, int V) {
-  return stats ? stats + r : reinterpret_cast<RowStat*>(cs.bid + (V + 3) / 4 * 4);
+  return stats ? stats + r
+               : reinterpret_cast<RowStat*>(reinterpret_cast<char*>(cs.bid) + (cut_stat_offset(V) - kCutIdsOffset));
 }
 
 __device__ __forceinline__ const float* cut_logits(const float* logits, int r, int rstride, int roff, int V) {
@@ -721,6 +717,7 @@ __global__ __launch_bounds__(kCutSegThreads) void cut_hist_kernel(const float* _
 // loaded together (V <= 8 kIdVecs kSampleThreads).
 constexpr int kIdVecs = 4;
 typedef uint32_t id8 __attribute__((ext_vector_type(4)));   // eight 16-bit bucket ids
+static_assert(alignof(id8) <= kCutAlign && kCutIdsOffset % alignof(id8) == 0, "bucket ids are read in aligned vectors");
 static_assert(8 * kIdVecs * kSampleThreads >= kPerLane * kSampleThreads, "bucket ids of the largest cut row");
 struct RowIds {
   id8 v[kIdVecs];
@@ -1994,7 +1991,7 @@ hipError_t launch_softmax(const float* logits, int rows, int V, float temperatur
   // (144 rows: 64.9 and 64.2); V = 8000 27.4 / 27.5 / 27.8 / 28.1 -> 22.2 /
   // 24.9 / 28.6 / 30.9, hence both bounds.
   if (apart && modifiers_active(temperature, top_k, top_p, V)) {
-    if (row_bytes >= cut_row_bytes(V) + 512 && (rows <= 8 || (V >= 16384 && rows <= 64))) {
+    if (cut_fits_output(V) && (rows <= 8 || (V >= 16384 && rows <= 64))) {
       int seg = 0, nseg = 0;
       const hipError_t e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, nullptr,
                                     reinterpret_cast<char*>(probs), row_bytes, err, &seg, &nseg, st);

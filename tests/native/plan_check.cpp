@@ -15,6 +15,8 @@
 //  * wide-GEMM plans cover their matrix; attention partials fit their region;
 //  * the sampling kernels' row segments tile every row, none empty, at most
 //    kMaxRowSegments per row;
+//  * the cut-off's scratch lies inside an output row, aligned, wherever the
+//    row starts;
 //  * config validation and the packed layout do no undefined arithmetic on
 //    extreme field values.
 #include <climits>
@@ -134,6 +136,28 @@ static void check_segments() {
     }
 }
 
+// The cut-off's scratch of a row: at every 4-byte address an output row can
+// start at, aligned for the widest access to each part (16-byte vectors of
+// bucket ids, 8-byte fields elsewhere) and inside the row; in a workspace,
+// inside cut_row_bytes.
+static void check_cut_scratch() {
+  for (int V = 1; V <= modifier_max_vocab(); ++V) {
+    const size_t ids = (static_cast<size_t>(V) + 7) / 8 * 16;      // as read: whole vectors
+    CHECK(kCutIdsOffset + ids <= cut_row_bytes(V), "V %d: bucket ids past the workspace row", V);
+    if (!cut_fits_output(V)) continue;
+    for (uintptr_t row = 4096; row < 4096 + 64; row += 4) {
+      const uintptr_t p = row + cut_row_shift(row), end = row + static_cast<size_t>(V) * 4;
+      CHECK(p >= row && p % 8 == 0 && (p + kCutPartOffset) % 8 == 0, "V %d row +%zu: histogram", V, row % 64);
+      CHECK((p + kCutIdsOffset) % 16 == 0, "V %d row +%zu: bucket ids off their vector alignment", V, row % 64);
+      CHECK((p + cut_stat_offset(V)) % 8 == 0 && cut_stat_offset(V) >= kCutIdsOffset + 2 * static_cast<size_t>(V),
+            "V %d row +%zu: statistics", V, row % 64);
+      CHECK(p + kCutIdsOffset + ids <= end && p + cut_stat_offset(V) + kRowStatBytes <= end,
+            "V %d row +%zu: scratch past the row", V, row % 64);
+    }
+  }
+  CHECK(kCutPartOffset >= kCutBuckets * 2 * sizeof(uint64_t) && kCutIdsOffset >= kCutPartOffset + 256, "scratch parts overlap");
+}
+
 static void check_extremes() {
   const int vals[] = {INT_MIN, -1, 0, 1, 2, 31, 32, 64, 128, 4096, 16384, 16416, 1 << 20, (1 << 24) - 1, 1 << 24,
                       INT_MAX};
@@ -192,6 +216,7 @@ int main() {
   for (const auto& s : shapes) check_shape(s.c, s.name);
   check_wide_plans();
   check_segments();
+  check_cut_scratch();
   check_extremes();
   if (failures) {
     std::fprintf(stderr, "%d failures\n", failures);
