@@ -188,8 +188,11 @@ size_t cut_row_bytes(int V) {
   return align256(kCutIdsOffset + static_cast<size_t>(V) * 2);
 }
 
-bool cut_fits_output(int V) {
-  return V <= modifier_max_vocab() && static_cast<size_t>(V) * 4 >= cut_row_bytes(V) + 512;
+bool cut_fits_output(int rows, int V) {
+  if (V > modifier_max_vocab() || static_cast<size_t>(V) * 4 < cut_row_bytes(V) + 512) return false;
+  int seg = 0, nseg = 0;
+  cut_segments(rows, V, &seg, &nseg);
+  return V - (nseg - 1) * seg >= kStatEntries;     // the last segment is the shortest
 }
 
 WsLayout make_ws(const Layout& L, int B, int Mps, int T_cap) {

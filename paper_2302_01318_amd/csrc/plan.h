@@ -156,10 +156,14 @@ constexpr size_t kCutPartOffset = (static_cast<size_t>(kCutBuckets) * 2 * 8 + 25
 constexpr size_t kCutIdsOffset = kCutPartOffset + 256;
 constexpr size_t cut_row_shift(uintptr_t row) { return (kCutAlign - row % kCutAlign) % kCutAlign; }
 constexpr size_t cut_stat_offset(int V) { return kCutIdsOffset + (static_cast<size_t>(V) + 3) / 4 * 8; }
+// sps_softmax leaves a row's statistics at the head of each of its segments of
+// the output, where that segment's work-group finds them: entries they take.
+constexpr int kStatEntries = static_cast<int>(kRowStatBytes / 4);
 // Bytes of a row's scratch in a workspace; 0 where the vocabulary is past what the cut-off handles.
 size_t cut_row_bytes(int V);
-// Whether rows of V fp32 outputs hold that scratch wherever they start.
-bool cut_fits_output(int V);
+// Whether `rows` output rows of V fp32 entries hold that scratch wherever
+// they start, and every segment of theirs the statistics.
+bool cut_fits_output(int rows, int V);
 
 // Segments of a row for the sampling kernels that take one segment per
 // work-group (the cut-off's histogram, the draft export): about 512

@@ -1005,7 +1005,8 @@ __global__ __launch_bounds__(kSampleThreads) void cut_select_kernel(const float*
   const RowStat base = *cut_stat(stats, cs, r, V); // merged by cut_hist_kernel
   // The statistics for whoever exports the row: into the array or, where the
   // scratch is the output row itself (no array), to the head of each of its
-  // segments, which only that segment's work-group reads and overwrites.
+  // segments (kStatEntries entries or more: cut_fits_output), which only that
+  // segment's work-group reads and overwrites.
   auto leave = [&](const RowStat& st) {
     if (stats) {
       if (threadIdx.x == 0) stats[r] = st;
@@ -1014,11 +1015,11 @@ __global__ __launch_bounds__(kSampleThreads) void cut_select_kernel(const float*
     __syncthreads();                               // the scratch is read no more
     const int s = threadIdx.x;
     if (s * copy_seg < V) {
-      uint32_t w[sizeof(RowStat) / 4];
+      uint32_t w[kStatEntries];
       __builtin_memcpy(w, &st, sizeof(st));
       uint32_t* head = reinterpret_cast<uint32_t*>(cut + static_cast<size_t>(r) * cut_bytes) + s * copy_seg;
 #pragma unroll
-      for (unsigned i = 0; i < sizeof(RowStat) / 4; ++i) head[i] = w[i];
+      for (int i = 0; i < kStatEntries; ++i) head[i] = w[i];
     }
   };
   if (base.nonfinite) {                            // uniform: one-hot at index 0, never cut (as row_stat_final)
@@ -1065,9 +1066,9 @@ __global__ __launch_bounds__(kCutSegThreads) void cut_export_kernel(const float*
   const int r = blockIdx.y, i0 = blockIdx.x * seg, i1 = min(V, i0 + seg);
   float* pr = probs + static_cast<size_t>(r) * V;
   RowStat st;
-  uint32_t w[sizeof(RowStat) / 4];
+  uint32_t w[kStatEntries];
 #pragma unroll
-  for (unsigned i = 0; i < sizeof(RowStat) / 4; ++i) w[i] = __float_as_uint(pr[i0 + i]);
+  for (int i = 0; i < kStatEntries; ++i) w[i] = __float_as_uint(pr[i0 + i]);
   __builtin_memcpy(&st, w, sizeof(st));
   __syncthreads();                                 // every thread has it before any entry is written
   const float* z = logits + static_cast<size_t>(r) * V;
@@ -1991,7 +1992,7 @@ hipError_t launch_softmax(const float* logits, int rows, int V, float temperatur
   // (144 rows: 64.9 and 64.2); V = 8000 27.4 / 27.5 / 27.8 / 28.1 -> 22.2 /
   // 24.9 / 28.6 / 30.9, hence both bounds.
   if (apart && modifiers_active(temperature, top_k, top_p, V)) {
-    if (cut_fits_output(V) && (rows <= 8 || (V >= 16384 && rows <= 64))) {
+    if (cut_fits_output(rows, V) && (rows <= 8 || (V >= 16384 && rows <= 64))) {
       int seg = 0, nseg = 0;
       const hipError_t e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, nullptr,
                                     reinterpret_cast<char*>(probs), row_bytes, err, &seg, &nseg, st);

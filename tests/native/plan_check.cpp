@@ -19,6 +19,7 @@
 //    row starts;
 //  * config validation and the packed layout do no undefined arithmetic on
 //    extreme field values.
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstdio>
@@ -144,7 +145,7 @@ static void check_cut_scratch() {
   for (int V = 1; V <= modifier_max_vocab(); ++V) {
     const size_t ids = (static_cast<size_t>(V) + 7) / 8 * 16;      // as read: whole vectors
     CHECK(kCutIdsOffset + ids <= cut_row_bytes(V), "V %d: bucket ids past the workspace row", V);
-    if (!cut_fits_output(V)) continue;
+    if (!cut_fits_output(1, V)) continue;
     for (uintptr_t row = 4096; row < 4096 + 64; row += 4) {
       const uintptr_t p = row + cut_row_shift(row), end = row + static_cast<size_t>(V) * 4;
       CHECK(p >= row && p % 8 == 0 && (p + kCutPartOffset) % 8 == 0, "V %d row +%zu: histogram", V, row % 64);
@@ -155,6 +156,19 @@ static void check_cut_scratch() {
             "V %d row +%zu: scratch past the row", V, row % 64);
     }
   }
+  // Every segment of an admitted output row holds the statistics left at its
+  // head. (Stated from the segments themselves: the shortest of them.)
+  for (int rows = 1; rows <= 64; ++rows)
+    for (int V = 1; V <= modifier_max_vocab(); ++V) {
+      if (!cut_fits_output(rows, V)) continue;
+      int seg = 0, nseg = 0, shortest = V;
+      cut_segments(rows, V, &seg, &nseg);
+      for (int s = 0; s < nseg; ++s) shortest = std::min(shortest, std::min(V, (s + 1) * seg) - s * seg);
+      CHECK(shortest * 4 >= static_cast<int>(kRowStatBytes), "rows %d V %d: a segment of %d entries", rows, V, shortest);
+    }
+  CHECK(cut_fits_output(1, 4736) && cut_fits_output(64, 16384) && cut_fits_output(8, modifier_max_vocab()) &&
+            !cut_fits_output(1, modifier_max_vocab() + 1) && !cut_fits_output(1, 1000),
+        "rows the cut-off runs in");
   CHECK(kCutPartOffset >= kCutBuckets * 2 * sizeof(uint64_t) && kCutIdsOffset >= kCutPartOffset + 256, "scratch parts overlap");
 }
 
