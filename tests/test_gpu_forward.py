@@ -191,6 +191,32 @@ def test_long_prefill_chunk_parity(sps, dtype, tol, B, M):
     assert sps.device_error() == 0
 
 
+@pytest.mark.parametrize("B,M,prior", [(1, 160, 0), (1, 96, 40), (2, 80, 17), (3, 20, 0)])
+def test_prefill_scratch_follows_the_length(sps, B, M, prior):
+    """A prefill chunk into a cache of 4096 positions leaves the keys and
+    values that one of 256 leaves, bit for bit, whatever its workspace held
+    (every byte 0xff: NaN), and writes no more of it than the smaller cache's
+    whole workspace: the attention partials of positions that do not exist
+    yet are neither written nor read."""
+    shape = SMALL.with_(ffn="swiglu")
+    print("prefill scratch", B, M, prior, flush=True)
+    gm, _ = build_pair(shape, 8)
+    toks = torch.from_numpy(synth.tokens(10, B, M, shape.vocab)).cuda()
+    caches, sizes = [], []
+    for T in (256, 4096):
+        kv = sps.KVCache(shape, B, T)
+        install_prior(shape, kv, new_cache(shape, B, T), 9, [prior] * B)
+        ws = torch.full((sps.lib.sps_prefill_workspace_bytes(ctypes.byref(kv.cfg), B, M, T),), 255, dtype=torch.uint8,
+                        device="cuda")
+        assert sps.lib.sps_prefill(gm.handle, kv.handle, toks.data_ptr(), M, B, M, 0, ws.data_ptr(), ws.numel(), None) == 0
+        torch.cuda.synchronize()
+        sizes.append((ws.numel(), int((ws != 255).sum())))
+        caches.append([x for layer in range(shape.n_layers) for b in range(B) for x in kv.read(layer, b, 0, prior + M)])
+    assert all(torch.equal(a, b) for a, b in zip(*caches))
+    assert sizes[1][1] <= sizes[0][0] < sizes[1][0] // 2, sizes
+    assert sps.device_error() == 0
+
+
 def test_capacity_overflow_is_flagged(sps):
     """Positions past the cache capacity: the writes are skipped, the device
     flag is raised, and nothing faults."""
