@@ -27,7 +27,9 @@ TORCH_DTYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "fp8": torch.bfloat
 TENSOR_ID = {"embed": 0, "final_norm": 1, "unembed": 2, "attn_norm": 3, "wq": 4, "wk": 5, "wv": 6,
              "wo": 7, "ffn_norm": 8, "w1": 9, "w3": 10, "w2": 11}
 PURPOSE_DRAFT, PURPOSE_ACCEPT, PURPOSE_RESAMPLE = 0, 1, 2
-# Rows (sequences x tokens) of the Generator's prefill chunks.
+# Rows (sequences x tokens) one prefill chunk can have, and the workspace that
+# chunks of more than a forward's 64 tokens may take (their attention partials
+# grow with the rows and the cache capacity).
 PREFILL_ROWS = 160
 PREFILL_BYTES = 2 << 30
 DEV_BAD_TOKEN, DEV_EMPTY, DEV_CAPACITY, DEV_NONFINITE = 1, 2, 4, 8
@@ -225,6 +227,19 @@ def workspace(shape, B, max_tokens_per_seq, T_cap, device="cuda", prefill_tokens
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 
+def prefill_tokens(shapes, B, T_cap, at_most=None):
+    """Tokens per sequence of a prefill chunk of B sequences into caches of
+    T_cap positions: what PREFILL_ROWS rows hold (a chunk streams every weight
+    once), no more than the caller's bound, nor, past a forward's 64 tokens,
+    than the caches hold or PREFILL_BYTES of workspace allow."""
+    n = max(1, PREFILL_ROWS // B) if at_most is None else max(1, min(at_most, PREFILL_ROWS // B))
+    n = min(n, max(64, T_cap))
+    if n > 64 and any(lib.sps_prefill_workspace_bytes(ctypes.byref(config_of(s)), B, n, T_cap) > PREFILL_BYTES
+                      for s in shapes):
+        n = 64
+    return n
+
+
 def forward(model, kv, tokens, M, pos_offset=0, logits=None, ws=None, tok_stride=None):
     B = kv.B
     check(lib.sps_forward(model.handle, kv.handle, _ptr(tokens, torch.int32, "tokens"),
@@ -356,7 +371,9 @@ class Generator:
     except an end-of-output check every `check_every` loops. K = 0 without a
     draft model is auto-regressive sampling (Algorithm 1)."""
 
-    def __init__(self, target, draft, B, T_cap, K, device="cuda", prefill_chunk=64):
+    def __init__(self, target, draft, B, T_cap, K, device="cuda", prefill_chunk=None):
+        """prefill_chunk: at most this many tokens per sequence in one prefill
+        forward (None: as many as prefill_tokens finds room for)."""
         if draft is not None and draft.shape.vocab != target.shape.vocab:
             # p_t and q_t are distributions over one token space (the accept
             # ratio q(x)/p(x) of Algorithm 2); the draft's p rows are read at
@@ -364,16 +381,7 @@ class Generator:
             raise ValueError("draft vocabulary %d differs from the target's %d"
                              % (draft.shape.vocab, target.shape.vocab))
         self.target, self.draft, self.B, self.K, self.T_cap = target, draft, B, K, T_cap
-        # Tokens per sequence of a prefill chunk: prefill_chunk up to the 64 of
-        # a forward, and from there (the default) what fits a prefill's rows,
-        # unless the attention partials of so many rows over a very long cache
-        # would take more than PREFILL_BYTES.
-        self.chunk = max(1, min(prefill_chunk, 160 // B, 64))
-        if prefill_chunk >= 64:
-            rows = PREFILL_ROWS // B
-            if max(lib.sps_prefill_workspace_bytes(ctypes.byref(config_of(m.shape)), B, max(rows, 1), T_cap)
-                   for m in (target, draft) if m is not None) <= PREFILL_BYTES:
-                self.chunk = max(self.chunk, rows)
+        self.chunk = prefill_tokens([m.shape for m in (target, draft) if m is not None], B, T_cap, prefill_chunk)
         mps = max(min(self.chunk, 64), K + 1, 2)
         self.lengths = torch.zeros(B, dtype=torch.int32, device=device)
         self.kv_t = KVCache(target.shape, B, T_cap, self.lengths, device)

@@ -192,3 +192,29 @@ def test_generator_refuses_a_draft_of_another_vocabulary(sps):
     with pytest.raises(ValueError, match="vocabulary"):
         sps.Generator(Fake(configs.TINY_TARGET), Fake(configs.TINY_DRAFT.with_(vocab=1000)), 1, 64, 4,
                       device="cpu")
+
+
+@pytest.mark.parametrize("B,T_cap,at_most,want", [
+    (1, 256, None, 160), (2, 256, None, 80), (3, 256, None, 53), (1, 32, None, 64), (1, 96, None, 96),
+    (1, 256, 64, 64), (1, 256, 100, 100), (1, 256, 7, 7), (1, 256, 0, 1), (1, 256, 1000, 160), (2, 256, 64, 64),
+    (4, 256, 64, 40), (1, 1 << 20, None, 64), (1, 1 << 20, 32, 32)])
+def test_generator_prefill_chunk(sps, monkeypatch, B, T_cap, at_most, want):
+    """prefill_chunk bounds the tokens of a prefill chunk, and the Generator's
+    workspace with them; by default a chunk has as many as 160 rows hold, but
+    past 64 no more than the cache and no more scratch than PREFILL_BYTES."""
+    shape = configs.DRAFT_70B if T_cap > 256 else configs.TINY_TARGET
+    assert sps.prefill_tokens([shape], B, T_cap, at_most) == want
+    if T_cap > 256:
+        return
+
+    class Fake:
+        pass
+    model = Fake()
+    model.shape = shape
+    monkeypatch.setattr(sps, "KVCache", lambda *a: None)          # wants device memory
+    args = {} if at_most is None else {"prefill_chunk": at_most}
+    gen = sps.Generator(model, None, B, T_cap, 4, device="cpu", **args)
+    c = ctypes.byref(sps.config_of(shape))
+    assert gen.chunk == want
+    assert gen.ws_t.numel() == max(sps.lib.sps_workspace_bytes(c, B, max(min(want, 64), 5), T_cap),
+                                   sps.lib.sps_prefill_workspace_bytes(c, B, want, T_cap))

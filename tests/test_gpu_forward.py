@@ -191,6 +191,34 @@ def test_long_prefill_chunk_parity(sps, dtype, tol, B, M):
     assert sps.device_error() == 0
 
 
+@pytest.mark.parametrize("B", [1, 2])
+def test_generator_prefill_over_several_chunks(sps, B, monkeypatch):
+    """Generator.prefill of 322 tokens (three or five chunks, the last short)
+    against the oracle's caches: by default, with a chunk of its caller's, and
+    where PREFILL_BYTES allows no more than 64 tokens at a time. The tokens a
+    chunk left behind are the next one's context; tol as for logits."""
+    shape = SMALL.with_(dtype="f32")
+    P, T = 322, 352
+    print("generator prefill", B, flush=True)
+    gm, W = build_pair(shape, 8)
+    toks = synth.tokens(10, B, P, shape.vocab)
+    ocache = new_cache(shape, B, T)
+    om.forward_cached(spec_of(shape), W, ocache, toks[:, :P - 1], np.zeros(B, np.int64))
+    for chunk, at_most, nbytes in ((160 // B, None, sps.PREFILL_BYTES), (50, 50, sps.PREFILL_BYTES), (64, None, 1)):
+        monkeypatch.setattr(sps, "PREFILL_BYTES", nbytes)
+        gen = sps.Generator(gm, None, B, T, 4, prefill_chunk=at_most)
+        assert gen.chunk == chunk
+        gen.prefill(torch.from_numpy(toks).cuda())
+        torch.cuda.synchronize()
+        assert gen.lengths.tolist() == [P - 1] * B and np.array_equal(gen.ctx.cpu().numpy(), toks[:, P - 2:])
+        for layer in range(shape.n_layers):
+            for b in range(B):
+                for got, name in zip(gen.kv_t.read(layer, b, 0, P - 1), "kv"):
+                    want = ocache[name][layer, b, :, :P - 1]
+                    assert np.abs(got.double().cpu().numpy() - want).max() <= 1e-4 * max(1.0, np.abs(want).max())
+        assert sps.device_error() == 0
+
+
 @pytest.mark.parametrize("B,M,prior", [(1, 160, 0), (1, 96, 40), (2, 80, 17), (3, 20, 0)])
 def test_prefill_scratch_follows_the_length(sps, B, M, prior):
     """A prefill chunk into a cache of 4096 positions leaves the keys and
