@@ -1500,21 +1500,24 @@ __global__ __launch_bounds__(kSampleThreads) void accept_kernel(QS qs, const flo
 }
 
 // The entry row that holds the threshold: lane l has the weights of entries
-// 64 k + l in v[k], off is the weight before them. Halves the range of k on
-// wave sums; leaves the chosen row's weights in v[0], its k added to k0 and
-// the weight before it in off.
+// 64 k + l in v[k], 256 more where bit k of big is set, off is the weight
+// before them. Halves the range of k on wave sums; leaves the chosen row's
+// weights in v[0] and bit 0 of big, its k added to k0 and the weight before it
+// in off.
 template <int WIDTH, int N>
-__device__ __forceinline__ void halve_to_entry(uint32_t (&v)[N], uint64_t thr, uint64_t& off, int& k0) {
+__device__ __forceinline__ void halve_to_entry(uint32_t (&v)[N], uint32_t& big, uint64_t thr, uint64_t& off, int& k0) {
   uint32_t lo = 0, hi = 0;
 #pragma unroll
   for (int k = 0; k < WIDTH; ++k) hi += __builtin_uadd_overflow(lo, v[k], &lo);
-  const uint64_t half = wave_sum_u64(static_cast<uint64_t>(hi) << 32 | lo);
+  const uint64_t half =
+      wave_sum_u64((static_cast<uint64_t>(hi) << 32 | lo) + (__popc(big & ((1u << WIDTH) - 1)) << 8));
   const bool up = off + half <= thr;
   off += up ? half : 0;
   k0 += up ? WIDTH : 0;
 #pragma unroll
   for (int k = 0; k < WIDTH; ++k) v[k] = up ? v[k + WIDTH] : v[k];
-  if constexpr (WIDTH > 1) halve_to_entry<WIDTH / 2>(v, thr, off, k0);
+  big >>= up ? WIDTH : 0;                  // (bits past the width in use are not looked at)
+  if constexpr (WIDTH > 1) halve_to_entry<WIDTH / 2>(v, big, thr, off, k0);
 }
 
 // fixed_weight of x < 1, in 32 bits (0 for NaN).
@@ -1528,8 +1531,7 @@ __device__ __forceinline__ uint32_t fixed_weight32(float x) {
 // it, and lane l keeps the draw weights of its entries 64 k + l, k < PER, in
 // registers. The segment totals name the wave whose segment holds the
 // threshold, and that wave alone halves its k range on wave sums and scans
-// one entry per lane. Rows with an entry of 1 or more (weight 2^32: one-hot
-// rows) and zero residuals take the two-pass draw. One work-group per
+// one entry per lane. Zero residuals take the two-pass draw. One work-group per
 // sequence (the call has no scratch to meet in), so what bounds it is the
 // chain of memory rounds (drafts, gathers, rows) and the VALU work of a row
 // on one CU. Against the two-pass draw over 64-bit weights (kernel time): 64
@@ -1599,24 +1601,54 @@ __global__ __launch_bounds__(kSampleThreads) void accept_probs_kernel(
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    const uint64_t tot = wave_sum_u64(static_cast<uint64_t>(tot_hi) << 32 | tot_lo);
+    uint64_t tot = wave_sum_u64(static_cast<uint64_t>(tot_hi) << 32 | tot_lo);
     if (lane == 0) s_tot[wave] = tot;
-    const bool one = __syncthreads_or(worst >= 0x3f800000u << 1);   // an entry of magnitude >= 1, or not finite
+    // Rows with an entry of magnitude 1 or more, or not finite: the waves that
+    // have one read theirs again (from the caches) for what the 32 bits miss.
+    // A target entry of 1 or more has weight 2^32, 256 more than fixed_weight32
+    // gives; where the draft's is one too, their difference is 0 either way.
+    // (One-hot rows of 32000, one sequence, K = 4, all drafts accepted / the
+    // first rejected: the two-pass draw alone 12.5 / 20.7 us, after the pass
+    // above 13.3 / 19.4, this 9.7 / 10.2.)
+    const bool mine = worst >= 0x3f800000u << 1;
+    bool nf = false;
+    uint32_t big = 0;
+    if (__syncthreads_or(mine)) {
+      static_assert(PER <= 32 && (PER == kB || PER % (2 * kB) == 0), "one bit per entry; whole batches");
+      if (__ballot(mine)) {
+#pragma unroll 1
+        for (int k0 = 0; k0 < PER; k0 += 2 * kB) {
+          load(k0, xq[0], xp[0]);
+          if (PER > kB) load(k0 + kB, xq[1], xp[1]);
+#pragma unroll
+          for (int j = 0; j < (PER > kB ? 2 : 1) * kB; ++j) {
+            const float vq = __uint_as_float(xq[j / kB][j % kB]), vp = __uint_as_float(xp[j / kB][j % kB]);
+            nf |= not_finite(vq) | not_finite(vp);
+            big |= vq >= 1.f && !(vp >= 1.f) ? 1u << (k0 + j) : 0;
+          }
+        }
+        tot += wave_sum_u64(__popc(big)) << 8;
+        if (lane == 0) s_tot[wave] = tot;
+      }
+      nf = __syncthreads_or(nf);
+    }
     uint64_t off = 0, W = 0;
     for (int v = 0; v < kSampleThreads / 64; ++v) {
       const uint64_t t = s_tot[v];
       off += v < wave ? t : 0;
       W += t;
     }
-    if (one || W == 0) {                   // uniform, as W and thr
+    if (nf) {                              // uniform, as W and thr
+      y = -2;
+    } else if (W == 0) {
       y = accept_draw<false>(qs.row(b * (K + 1) + a), p + (resid ? static_cast<size_t>(b) * K + a : 0) * V, resid, V,
                              s_u, s_tot, &s_y);
     } else {
       const uint64_t thr = grid_threshold(s_u, W);
       if (off <= thr && thr < off + tot) {   // wave-uniform: the crossing lies in this wave's segment
         int k0 = 0;
-        halve_to_entry<PER / 2>(w, thr, off, k0);
-        const uint64_t hit = __ballot(off + wave_incl_scan_u64(w[0]) > thr);
+        halve_to_entry<PER / 2>(w, big, thr, off, k0);
+        const uint64_t hit = __ballot(off + wave_incl_scan_u64(w[0] + (static_cast<uint64_t>(big & 1u) << 8)) > thr);
         if (lane == 0) s_y = b0 + 64 * k0 + __ffsll(static_cast<long long>(hit)) - 1;
       }
       __syncthreads();

@@ -156,6 +156,55 @@ def test_accept_row_lengths(sps, V):
     assert sps.device_error() == 0
 
 
+@pytest.mark.parametrize("V", [65, 1025, 8192, 8193, 32000, 32768])
+def test_accept_entries_of_one_and_more(sps, V):
+    """Rows with entries of magnitude 1 and more (weight 2^32 where positive),
+    one per sequence: one-hot rows accepted throughout (the bonus draw) and
+    rejected at once (the residual of two one-hot rows), target entries of 1
+    beside draft entries from 0 up to 1 and past it, such entries in most
+    segments of the row, and negative ones; over the whole range of u,
+    bit-exact against the oracle."""
+    K = 2
+    g = np.random.default_rng(V)
+    u = [0.0, 2.0 ** -24, 0.3, 0.5, 0.9, 1 - 2.0 ** -24]
+    kinds = [(k, x) for k in ("accepted", "rejected", "beside", "many", "negative") for x in u]
+    B = len(kinds)
+    z = g.normal(0, 2, size=(B, K + 1, V))
+    q = (np.exp(z) / np.exp(z).sum(-1, keepdims=True)).astype(np.float32)
+    p = (np.exp(z[:, :K]) / np.exp(z[:, :K]).sum(-1, keepdims=True)).astype(np.float32)
+    drafts = g.integers(0, V, (B, K)).astype(np.int32)
+    unif = np.zeros((B, K + 1), np.float32)
+    below = np.float32(1 - 2.0 ** -24)
+    for b, (kind, x) in enumerate(kinds):
+        unif[b] = [0.75, 0.75, x]
+        at = g.choice(V, 9, replace=False)
+        if kind in ("accepted", "rejected"):
+            q[b], p[b] = 0, 0
+            q[b, range(K + 1), at[:K + 1]] = 1
+            drafts[b] = at[:K] if kind == "accepted" else (at[:K] + 1) % V
+            p[b, range(K), drafts[b]] = 1
+            continue
+        unif[b, 0] = 1 - 2.0 ** -24                    # rejected: r p >= q at the first draft
+        drafts[b] = at[0]
+        p[b, :, at[0]], q[b, :, at[0]] = 0.5, 0.25
+        if kind == "beside":
+            q[b, :, at[1:9]] = np.float32([1, 1, 1, 1, 1, 1.5, 1, below])[:, None]
+            p[b, :, at[1:9]] = np.float32([0, 2.0 ** -32, 2.0 ** -31, 0.5, below, 1, 2, 1])[:, None]
+        elif kind == "many":
+            q[b, :, ::max(1, V // 50)] = 1
+            p[b, :, ::max(1, V // 7)] = np.float32(0.25)
+            p[b, :, at[0]] = 2
+        else:
+            q[b, :, at[1]], p[b, :, at[2]] = -1, -2
+            q[b, :, at[3]], p[b, :, at[3]] = 1, -1
+    out, nacc = run_accept(sps, p, q, drafts, unif)
+    w_out, w_n, _ = oacc.accept_resample(p, q, drafts, unif)
+    np.testing.assert_array_equal(out, w_out)
+    np.testing.assert_array_equal(nacc, w_n)
+    assert (nacc[:len(u)] == K).all() and (nacc[len(u):2 * len(u)] == 0).all()
+    assert sps.device_error() == 0
+
+
 def test_accept_k0_is_a_draw_from_q(sps):
     q = np.random.default_rng(5).dirichlet(np.ones(1000), size=(16, 1)).astype(np.float32)
     unif = np.linspace(0, 1, 16, endpoint=False, dtype=np.float32)[:, None]
