@@ -225,3 +225,20 @@ def test_softmax_over_several_cus_equals_in_place(sps, rows, V):
         assert (buf[:3] == -1).all() and (buf[3 + rows * V:] == -1).all()
     flags = sps.device_error()
     assert flags == (sps.DEV_NONFINITE if rows > 4 else 0)
+
+
+@pytest.mark.parametrize("k,p", [(0, 0.8), (8000, 1.0), (22000, 0.8), (8000, 0.9), (22000, 1.0)])
+def test_softmax_cut_in_a_flat_run(sps, k, p):
+    """Rows of 32000 whose cuts fall into a run of 16000 equal weights (above
+    it about 5000 larger ones): the nucleus alone, top-k alone, top-k below the
+    run and the nucleus in it, and top-k in it with the nucleus above it; in
+    one and over several CUs, against the oracle's cut."""
+    V = 32000
+    print("flat run top_k", k, "top_p", p, flush=True)
+    z = torch.from_numpy(np.random.default_rng(4).normal(0, 2, (3, V)).astype(np.float32)).cuda()
+    z[:, ::2] = 1.0
+    got = sps.softmax(z, 1.0, k, p)
+    base = sps.softmax(z, 1.0).cpu().numpy()
+    sps.softmax(z, 1.0, k, p, out=z)
+    np.testing.assert_array_equal(got.cpu().numpy(), z.cpu().numpy())
+    np.testing.assert_array_equal(got.cpu().numpy(), omod.modify_rows(base, k, p))
