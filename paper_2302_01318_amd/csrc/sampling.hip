@@ -133,9 +133,11 @@ __device__ __forceinline__ SoftPart thread_soft_part(const float* __restrict__ z
 }
 __device__ __forceinline__ void soft_merge(float& m, float& s2, float om, float os) {
 #pragma clang fp contract(off)
+  // (A select, not an early return: the merges of a row's partials then keep
+  // their loads together instead of waiting for one in each branch.)
   const float nm = fmaxf(m, om);
-  if (nm == -INFINITY) return;
-  s2 = __builtin_fmaf(os, expf(om - nm), s2 * expf(m - nm));
+  const float s = __builtin_fmaf(os, expf(om - nm), s2 * expf(m - nm));
+  s2 = nm == -INFINITY ? s2 : s;
   m = nm;
 }
 __device__ __forceinline__ void wave_soft_merge(float& m, float& s2) {
