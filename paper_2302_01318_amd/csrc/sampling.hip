@@ -2029,9 +2029,15 @@ hipError_t launch_softmax(const float* logits, int rows, int V, float temperatur
   // launches against one work-group per row, nucleus 0.95: V = 32000, 1 / 5 /
   // 20 / 64 rows 61.0 / 61.8 / 62.6 / 63.5 -> 27.1 / 29.1 / 36.8 / 43.0 us
   // (144 rows: 64.9 and 64.2); V = 8000 27.4 / 27.5 / 27.8 / 28.1 -> 22.2 /
-  // 24.9 / 28.6 / 30.9, hence both bounds.
+  // 24.9 / 28.6 / 30.9, hence the bounds on rows. On V, 1 / 8 rows: with one
+  // modifier 5003 23.4 / 23.8 -> 22.3 / 24.1, 5500 23.8 / 24.4 -> 22.0 / 24.4, 6000
+  // 24.7 / 25.1 -> 22.4 / 23.8; with both, whose selects run one after the other,
+  // 6000 29.2 / 29.5 -> 29.4 / 30.1, 7000 30.9 / 31.2 -> 29.1 / 31.7, 8000
+  // 31.9 / 32.5 -> 29.4 / 31.2.
   if (apart && modifiers_active(temperature, top_k, top_p, V)) {
-    if (cut_fits_output(rows, V) && (rows <= 8 || (V >= 16384 && rows <= 64))) {
+    const bool both = top_k >= 1 && top_k < V && top_p < 1.f;
+    const int least = rows <= 2 ? (both ? 7000 : 0) : rows <= 8 ? (both ? 8000 : 5500) : 16384;
+    if (cut_fits_output(rows, V) && rows <= 64 && V >= least) {
       int seg = 0, nseg = 0;
       const hipError_t e = cut_rows(logits, rows, 1, 0, V, temperature, top_k, top_p, nullptr,
                                     reinterpret_cast<char*>(probs), row_bytes, err, &seg, &nseg, st);

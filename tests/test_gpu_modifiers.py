@@ -242,3 +242,16 @@ def test_softmax_cut_in_a_flat_run(sps, k, p):
     sps.softmax(z, 1.0, k, p, out=z)
     np.testing.assert_array_equal(got.cpu().numpy(), z.cpu().numpy())
     np.testing.assert_array_equal(got.cpu().numpy(), omod.modify_rows(base, k, p))
+
+
+@pytest.mark.parametrize("rows,V", [(2, 4735), (2, 4736), (2, 6999), (2, 7000), (3, 5499), (3, 5500), (8, 7999), (8, 8000),
+                                    (9, 8000), (64, 16383), (64, 16384)])
+def test_softmax_cut_at_the_dispatch_lines(sps, rows, V):
+    """Both sides of each line of the rule that takes cut rows over several
+    CUs, with one modifier and with both: the oracle's cut, bit for bit."""
+    print("softmax lines rows", rows, "V", V, flush=True)
+    z = torch.randn(rows, V, generator=torch.Generator(device="cuda").manual_seed(V), device="cuda") * 2
+    base = sps.softmax(z, 0.8).cpu().numpy()
+    for k, p in ((0, 0.95), (40, 1.0), (40, 0.9)):
+        np.testing.assert_array_equal(sps.softmax(z, 0.8, k, p).cpu().numpy(), omod.modify_rows(base, k, p))
+    assert sps.device_error() == 0
