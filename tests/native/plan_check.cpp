@@ -7,11 +7,11 @@
 //    at its total;
 //  * the split-K partials of every launch a call can make (a draft step runs
 //    forwards of 2 and then 1 token per sequence within one layout; a verify
-//    step K + 1; a prefill chunk any count up to its maximum) fit the
+//    step K + 1; a prefill chunk any count up to the rows of a launch) fit the
 //    layout's partial region;
-//  * sps_workspace_bytes covers every layout a call with fewer tokens per
-//    sequence uses, and is 0 for requests no call admits (quickly: no loop
-//    over the requested count);
+//  * sps_workspace_bytes and sps_prefill_workspace_bytes cover every layout
+//    a call with fewer tokens per sequence uses, and are 0 for requests no
+//    call admits (quickly: no loop over the requested count);
 //  * wide-GEMM plans cover their matrix; attention partials fit their region;
 //  * the sampling kernels' row segments tile every row, none empty, at most
 //    kMaxRowSegments per row;
@@ -101,6 +101,24 @@ static void check_shape(const sps_config& c, const char* name) {
       }
       CHECK(workspace_bytes(&c, B, max_mps + 1, T_cap) == 0 || max_mps == kMaxTokensPerSeq,
             "%s: B %d x %d rows admitted", name, B, max_mps + 1);
+      // Prefill chunks past a forward's tokens, up to the rows of one launch;
+      // a workspace for more tokens takes every shorter chunk.
+      const int most = kMaxRows / B;
+      const int counts[] = {1, 16, 17, 32, 33, kMaxTokensPerSeq, kMaxTokensPerSeq + 1, most / 2, most - 1, most};
+      for (int mps : counts) {
+        if (mps < 1 || mps > most) continue;
+        const WsLayout w = make_ws(L, B, mps, T_cap);
+        check_layout(w, name);
+        const size_t bytes = prefill_workspace_bytes(&c, B, mps, T_cap);
+        CHECK(bytes >= w.total, "%s: prefill_workspace_bytes(B %d, %d) below its layout", name, B, mps);
+        for (int m = 1; m <= mps; ++m) {
+          check_call(L, B, m, w, T_cap, name);
+          CHECK(bytes >= make_ws(L, B, m, T_cap).total, "%s: prefill_workspace_bytes(B %d, %d) below the layout of %d",
+                name, B, mps, m);
+        }
+      }
+      CHECK(prefill_workspace_bytes(&c, B, most + 1, T_cap) == 0, "%s: prefill of B %d x %d rows admitted", name, B,
+            most + 1);
     }
   }
 }
@@ -203,6 +221,11 @@ static void check_extremes() {
   CHECK(workspace_bytes(&c, 1, 64, kMaxTCap + 32) == 0, "capacity past the largest admitted");
   CHECK(workspace_bytes(&c, 1, 64, INT_MAX) == 0, "INT_MAX capacity admitted");
   CHECK(workspace_bytes(&c, 1, 5, 31) == 0, "capacity below 32 admitted");
+  CHECK(prefill_workspace_bytes(&c, 1, kMaxRows, kMaxTCap) > 0 && prefill_workspace_bytes(&c, 1, kMaxRows, kMaxTCap + 32) == 0 &&
+            prefill_workspace_bytes(&c, 1, kMaxRows, 31) == 0 && prefill_workspace_bytes(&c, 1, INT_MAX, 2112) == 0 &&
+            prefill_workspace_bytes(&c, INT_MAX, 1, 2112) == 0 && prefill_workspace_bytes(&c, 0, 1, 2112) == 0 &&
+            prefill_workspace_bytes(&c, 1, 0, 2112) == 0,
+        "prefill requests at the limits");
   sps_sampling s{1.f, 0, 1.f};
   CHECK(check_sampling(s, 32000) == SPS_OK, "plain sampling refused");
   s.top_p = NAN;

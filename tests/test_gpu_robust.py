@@ -255,9 +255,9 @@ def test_vocabulary_past_the_multi_cu_sampling(sps):
 
 # ----------------------------------------------------------- non-finite --
 
-def test_softmax_nonfinite_rows(sps):
+@pytest.mark.parametrize("V", [1000, 12000, 32000])
+def test_softmax_nonfinite_rows(sps, V):
     g = np.random.default_rng(8)
-    V = 1000
     z = g.normal(0, 2, size=(7, V)).astype(np.float32)
     z[1, 17] = np.nan
     z[2, 3] = np.inf
@@ -265,7 +265,7 @@ def test_softmax_nonfinite_rows(sps):
     z[4, 500] = 3e38                    # overflows only when divided by T = 0.5
     z[5, :] = np.nan
     for T, k, pp in ((1.0, 0, 1.0), (0.5, 0, 1.0), (0.0, 0, 1.0), (1.0, 50, 0.9)):
-        print("softmax non-finite T", T, k, pp, flush=True)
+        print("softmax non-finite V", V, "T", T, k, pp, flush=True)
         sps.device_error()
         got = sps.softmax(cuda(z, torch.float32), T, k, pp).cpu().numpy()
         flags = sps.device_error()
@@ -287,11 +287,13 @@ def test_softmax_nonfinite_rows(sps):
                 np.testing.assert_allclose(got[ok], want[ok], rtol=2e-5, atol=1e-10)
 
 
-def test_accept_nonfinite_inputs_bit_exact(sps):
+@pytest.mark.parametrize("V", [1000, 32000])
+def test_accept_nonfinite_inputs_bit_exact(sps, V):
     """Sequences with a NaN / Inf among the values the accept tests or the
     final draw read get a = 0 and token 0; the others are untouched; all
     bit-exact against the oracle's definition."""
-    B, K, V = 8, 4, 1000
+    B, K = 8, 4
+    print("accept non-finite V", V, flush=True)
     p, q, drafts = synth.accept_case(60, B, K, V, 2.0, 0.5)
     unif = np.random.default_rng(61).random((B, K + 1)).astype(np.float32)
     q[1, 3, drafts[1, 3]] = np.nan          # a late gathered q value
@@ -299,7 +301,8 @@ def test_accept_nonfinite_inputs_bit_exact(sps):
     q[3, :, 11] = np.nan                    # every q row (the draw reads one of them)
     p[4, :, 12] = -np.inf                   # every p row (a residual draw reads one)
     q[5, K, 0] = np.nan                     # the bonus row only
-    drafts[6, 1] = V + 3                    # a bad token, not non-finite
+    drafts[6, 1] = V + 3                    # a bad token, not non-finite, past an accepted one
+    unif[6, 0] = 0
     sps.device_error()
     out, nacc = sps.accept_resample(cuda(p, torch.float32), cuda(q, torch.float32), cuda(drafts, torch.int32),
                                     cuda(unif, torch.float32))
@@ -369,6 +372,12 @@ def test_verify_step_nonfinite_logits(sps, top_k, top_p):
     for j in range(K + 1):
         assert np.isnan(l1[1, j]).any()
         assert q1[1, j, 0] == 1.0 and not q1[1, j, 1:].any()
+    # The flag alone: without the accept stage, with and without the q rows.
+    for q in (None, torch.empty((B, K + 1, V), device="cuda")):
+        assert sps.device_error() == 0
+        sps.verify_step(gm, kv, cuda(toks, torch.int32), K, 1.0, ws, q=q, top_k=top_k, top_p=top_p)
+        torch.cuda.synchronize()
+        assert sps.device_error() == sps.DEV_NONFINITE
 
 
 @pytest.mark.parametrize("top_k,top_p", [(0, 1.0), (20, 0.9)])
