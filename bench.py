@@ -668,7 +668,7 @@ def accept_grid(args):
 
 
 def softmax_rows(args):
-    """sps_softmax alone (one work-group per row) on 5 rows of 32000 logits
+    """sps_softmax alone (several CUs per row) on 5 rows of 32000 logits
     ~ N(0, 2^2), the verify step's row count at K = 4: plain, nucleus 0.8
     and top-k 50 at --temperature; four input sets used in turn."""
     import torch

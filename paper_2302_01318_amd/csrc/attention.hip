@@ -358,7 +358,8 @@ static hipError_t attn_t(const void* q, const void* kc, const void* vc, const in
   }
   // Prefill chunks: query groups of 2 or 4 tiles, every wave writing its own
   // partial. (One launch over the three groups of a 160-token chunk: 57 -> 36 us
-  // with the merge against a launch pair per group, 7B at 1000 positions.)
+  // with the merge against a launch pair per group, 7B at 1000 positions in a cache
+  // of 1088.)
   const float c_log2 = 1.4426950408889634f / sqrtf(static_cast<float>(DH));
   const int groups = (T_cap + 4 * kWavePos - 1) / (4 * kWavePos);
   const T* qq = static_cast<const T*>(q);
